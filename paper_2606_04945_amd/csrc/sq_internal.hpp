@@ -148,6 +148,12 @@ hipError_t launch_tac_quant(const uint16_t* Z, const uint16_t* Mb, const uint16_
 hipError_t launch_transform(const uint16_t* X, const uint8_t* state, const float* P,
                             int M, int K, int dm, int du, float* Xp, hipStream_t st);
 
+// The same with k split over the waves of a workgroup (transform_split.hip), for
+// few rows: whether that is the faster form, and its launch (P given, X under 2 GiB).
+bool transform_split_faster(int M, int K);
+hipError_t launch_transform_split(const uint16_t* X, const uint8_t* state, const float* P, int M, int K, int dm,
+                                  int du, float* Xp, hipStream_t st);
+
 hipError_t launch_quant_f32(const float* x, int M, int K, uint8_t* q, float* s, hipStream_t st, int bits);
 
 hipError_t launch_quant_f16(const uint16_t* x, const uint8_t* state, int M, int K, int dm, int du,

@@ -605,21 +605,6 @@ __global__ __launch_bounds__(64 * (kTqMaxConsumerWaves + 1)) void tac_quant_kern
 constexpr int kTqmTok = 16;
 constexpr int kTqmMaxWaves = 8;
 
-// Lanes 16 r + k (row r = 0..3 of the wave, k = 0..15) hold x_0 .. x_3; on
-// return lane 16 r + k holds in x_p what lane 16 p + k held in x_r.  Two
-// rounds of lane-half / lane-row swaps.
-__device__ __forceinline__ void transpose_rows4(uint32_t& x0, uint32_t& x1, uint32_t& x2, uint32_t& x3) {
-    auto s02 = __builtin_amdgcn_permlane32_swap(x0, x2, false, false);
-    auto s13 = __builtin_amdgcn_permlane32_swap(x1, x3, false, false);
-    x0 = s02[0], x2 = s02[1], x1 = s13[0], x3 = s13[1];
-    auto s01 = __builtin_amdgcn_permlane16_swap(x0, x1, false, false);
-    auto s23 = __builtin_amdgcn_permlane16_swap(x2, x3, false, false);
-    x0 = s01[0], x1 = s01[1], x2 = s23[0], x3 = s23[1];
-}
-
-__device__ __forceinline__ float lo_h(uint32_t x) { return h2f((uint16_t)(x & 0xFFFFu)); }
-__device__ __forceinline__ float hi_h(uint32_t x) { return h2f((uint16_t)(x >> 16)); }
-
 template <int NG>
 struct TqmShape {
     static constexpr int kCWV = 16 * NG;                        // channels per wave

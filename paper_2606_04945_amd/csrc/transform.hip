@@ -18,14 +18,15 @@
 // 16 x 16, each output with a chunk accumulator (the instruction's result
 // registers) and a total: 128 x 128 tiles of eight waves of 32 x 64 (four waves
 // per SIMD at two workgroups per CU; four waves of 64 x 64 were 3-9 % slower),
-// 64 x 128 tiles of four waves where 128-row tiles would leave CUs idle, and
-// 32 x 256 for up to 32 rows.  Main kernel: both operand tiles go from HBM straight
+// 64 x 128 tiles of four waves where 128-row tiles would leave CUs idle.  Calls
+// that 64 x 128 tiles would leave with too few workgroups (up to 32 rows, a few
+// hundred at the usual widths) split k over a workgroup's waves instead
+// (transform_split.hip).  Both operand tiles go from HBM straight
 // into LDS (buffer loads with the LDS destination, no staging registers)
 // through a three-stage ring, two k steps of 32 in flight while a third is
 // multiplied, one barrier per step; X stays fp16 in LDS and is widened as it is
 // read.  Staging the tiles through registers instead (converting X on the way)
-// ran at 0.75 of the speed on the 8 x 2048-token shapes; that form remains for
-// batches of up to 32 rows.
+// ran at 0.75 of the speed on the 8 x 2048-token shapes.
 //
 // Rows grouped by state (the paper's split of the batch into masked and
 // unmasked tokens, Eq. 7): when some 128-column tile lies wholly inside one of
@@ -79,13 +80,6 @@ __device__ int group_rows(const uint8_t* __restrict__ state, int M, int rt, int*
     return nm;
 }
 
-// fp16 pair -> two fp32 (exact), low half first; the asm keeps the conversion
-// where the value is staged instead of next to its load.
-__device__ __forceinline__ void h2f_pair(uint32_t w, float& lo, float& hi) {
-    asm volatile("v_cvt_f32_f16_e32 %0, %2\n\tv_cvt_f32_f16_sdwa %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_1"
-                 : "=&v"(lo), "=&v"(hi) : "v"(w));
-}
-
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // v_mfma_f32_16x16x4_f32: D = C + sum_k A[:, k] B[k, :] over its four k as a
@@ -94,175 +88,13 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // four k is the chunk chain itself.  Lane l supplies A[l % 16][l / 16] and
 // B[l / 16][l % 16]; result register v holds row 4 (l / 16) + v, column l % 16.
 // A wave owns IB x JB blocks of 16 x 16 outputs, a workgroup WR x WC waves.
-template <int IB, int JB, int WR, int WC>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) void transform_kernel(
-    const uint16_t* __restrict__ X, const uint8_t* __restrict__ state, const float* __restrict__ P,
-    int M, int K, int dm, int du, int grouped, float* __restrict__ Xp) {
-    static_assert(WR * WC * kWave == kThreads, "four waves");
-    constexpr int BM = 16 * IB * WR;
-    constexpr int BN = 16 * JB * WC;
-    constexpr int AP = BM + 4;                       // padded LDS row (k-major A tile)
-    constexpr int BP = BN + 4;
-    __shared__ float As[2][kBK][AP];
-    __shared__ float Bs[2][kBK][BP];
-    __shared__ int rowmap[BM];
-    __shared__ int scan[kThreads];
-
-    const int tid = threadIdx.x;
-    const int lane = tid % kWave, wave = tid / kWave;
-    const int wr = wave / WC, wc = wave % WC;
-    int rt, ct;
-    const int R = (M + BM - 1) / BM;
-    xcd_tile(blockIdx.x, R, (K + BN - 1) / BN, R < 16 ? R : 16, rt, ct);
-    const int row0 = rt * BM, col0 = ct * BN;
-    if (grouped) {
-        const int nm = group_rows<BM>(state, M, rt, rowmap, scan);
-        const int rows_end = min(M, row0 + BM);
-        const bool all_m = rows_end <= nm, all_u = row0 >= nm;
-        const bool dropped = (all_m && col0 >= K - du) ||
-                             (all_u && col0 >= K - dm - du && col0 + BN <= K - du);
-        if (dropped) {
-            const int ncol4 = min(BN, K - col0) / 4;
-            for (int e = tid; e < BM * ncol4; e += kThreads) {
-                const int r = rowmap[e / ncol4];
-                if (r >= 0)
-                    *reinterpret_cast<float4*>(Xp + (size_t)r * K + col0 + (e % ncol4) * 4) =
-                        make_float4(0.f, 0.f, 0.f, 0.f);
-            }
-            return;
-        }
-    } else {
-        if (tid < BM) rowmap[tid] = row0 + tid < M ? row0 + tid : -1;
-        __syncthreads();
-    }
-
-    constexpr int VPR = kBK / 8;
-    constexpr int AV = (BM * VPR + kThreads - 1) / kThreads;
-    uint4 ra[AV];
-    constexpr int NB = kBK * BN / 4 / kThreads;
-    float4 rb[NB];
-    int arow[AV];
-    const uint16_t* aptr[AV];
-#pragma unroll
-    for (int v = 0; v < AV; ++v) {
-        const int e = tid + v * kThreads;
-        arow[v] = e < BM * VPR ? rowmap[e / VPR] : -1;
-        aptr[v] = X + (size_t)(arow[v] >= 0 ? arow[v] : 0) * K + (e % VPR) * 8;
-    }
-    bool bok[NB];
-    const float* bptr[NB];
-#pragma unroll
-    for (int v = 0; v < NB; ++v) {
-        const int e = tid + v * kThreads;
-        const int kr = e / (BN / 4), c4 = (e % (BN / 4)) * 4;
-        bok[v] = col0 + c4 < K;
-        bptr[v] = P + (size_t)kr * K + (bok[v] ? col0 + c4 : 0);
-    }
-    auto load_tiles = [&](int k0) {
-#pragma unroll
-        for (int v = 0; v < AV; ++v)
-            if (BM * VPR >= (v + 1) * kThreads || tid + v * kThreads < BM * VPR)
-                ra[v] = *reinterpret_cast<const uint4*>(aptr[v] + k0);
-#pragma unroll
-        for (int v = 0; v < NB; ++v) rb[v] = *reinterpret_cast<const float4*>(bptr[v] + (size_t)k0 * K);
-    };
-    auto store_tiles = [&](int buf) {
-#pragma unroll
-        for (int v = 0; v < AV; ++v) {
-            const int e = tid + v * kThreads;
-            if (e < BM * VPR) {
-                const int r = e / VPR, h = e % VPR;
-                const uint4 w = arow[v] >= 0 ? ra[v] : make_uint4(0, 0, 0, 0);
-                const uint32_t wv[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    float lo, hi;
-                    h2f_pair(wv[q], lo, hi);
-                    As[buf][h * 8 + 2 * q][r] = lo;
-                    As[buf][h * 8 + 2 * q + 1][r] = hi;
-                }
-            }
-        }
-#pragma unroll
-        for (int v = 0; v < NB; ++v) {
-            const int e = tid + v * kThreads;
-            const int kr = e / (BN / 4), c4 = (e % (BN / 4)) * 4;
-            *reinterpret_cast<float4*>(&Bs[buf][kr][c4]) = bok[v] ? rb[v] : make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-    };
-
-    f32x4 acc[IB][JB], tot[IB][JB];
-#pragma unroll
-    for (int i = 0; i < IB; ++i)
-#pragma unroll
-        for (int j = 0; j < JB; ++j)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.0f, tot[i][j][v] = 0.0f;
-
-    const int kl = lane / 16, il = lane % 16;
-    const int arow0 = wr * 16 * IB + il;             // A operand row of this lane in block 0
-    const int bcol0 = wc * 16 * JB + il;             // B operand column of this lane in block 0
-    const int nk = K / kBK;
-    load_tiles(0);
-    store_tiles(0);
-    __syncthreads();
-    for (int kt = 0; kt < nk; ++kt) {
-        const int buf = kt & 1;
-        if (kt + 1 < nk) load_tiles((kt + 1) * kBK);
-#pragma unroll
-        for (int s4 = 0; s4 < kBK / 4; ++s4) {
-            const int kk = 4 * s4 + kl;
-            float a[IB], b[JB];
-#pragma unroll
-            for (int i = 0; i < IB; ++i) a[i] = As[buf][kk][arow0 + 16 * i];
-#pragma unroll
-            for (int j = 0; j < JB; ++j) b[j] = Bs[buf][kk][bcol0 + 16 * j];
-#pragma unroll
-            for (int i = 0; i < IB; ++i)
-#pragma unroll
-                for (int j = 0; j < JB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[j], acc[i][j], 0, 0, 0);
-        }
-        const int kend = (kt + 1) * kBK;
-        if (kend % kChunk == 0 || kend == K) {       // chunk boundary: fold into the total
-#pragma unroll
-            for (int i = 0; i < IB; ++i)
-#pragma unroll
-                for (int j = 0; j < JB; ++j)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) tot[i][j][v] = tot[i][j][v] + acc[i][j][v], acc[i][j][v] = 0.0f;
-        }
-        if (kt + 1 < nk) {
-            store_tiles(buf ^ 1);
-            __syncthreads();
-        }
-    }
-
-    // result register v of block (i, j): tile row 16 (IB wr + i) + 4 (lane / 16) + v,
-    // tile column 16 (JB wc + j) + lane % 16; 16 lanes store 64 contiguous bytes of a row
-#pragma unroll
-    for (int i = 0; i < IB; ++i)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int r = rowmap[wr * 16 * IB + 16 * i + 4 * kl + v];
-            if (r < 0) continue;
-            const bool masked = state ? state[r] != 0 : false;
-#pragma unroll
-            for (int j = 0; j < JB; ++j) {
-                const int col = col0 + wc * 16 * JB + 16 * j + il;
-                if (col >= K) continue;
-                const bool keep = !state || kept(col, K, dm, du, masked);
-                Xp[(size_t)r * K + col] = keep ? tot[i][j][v] : 0.0f;
-            }
-        }
-}
-
-// The same computation with both operand tiles copied from HBM straight into
-// LDS (buffer loads with the LDS destination, no staging registers) through a
-// three-stage ring: two k steps are in flight while a third is multiplied, one
-// barrier per step.  X stays fp16 in LDS (64 bytes per row and step, its four
-// 16-byte chunks XOR-swizzled by row) and is widened when read; P is staged
-// as it is in HBM, 512 bytes per k row, its 16-byte chunks XOR-swizzled by k
-// so that the four k of an instruction fall on different banks.
+// Both operand tiles are copied from HBM straight into LDS (buffer loads with
+// the LDS destination, no staging registers) through a three-stage ring: two k
+// steps are in flight while a third is multiplied, one barrier per step.  X
+// stays fp16 in LDS (64 bytes per row and step, its four 16-byte chunks
+// XOR-swizzled by row) and is widened when read; P is staged as it is in HBM,
+// 512 bytes per k row, its 16-byte chunks XOR-swizzled by k so that the four k
+// of an instruction fall on different banks.
 template <int IB, int JB, int WR, int WC, int NT = 64 * WR * WC>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT / 128))) void transform_dma_kernel(
     const uint16_t* __restrict__ X, const uint8_t* __restrict__ state, const float* __restrict__ P,
@@ -454,16 +286,7 @@ hipError_t launch_transform(const uint16_t* X, const uint8_t* state, const float
         hipLaunchKernelGGL(gate_copy_kernel, dim3(blocks), dim3(kThreads), 0, st, X, state, M, K, dm, du, Xp);
         return hipGetLastError();
     }
-    // up to 32 rows: the register-staged kernel on 32 x 256 tiles
-    if (M <= 32) {
-        const int ncol = (K + 255) / 256;
-        const int u0 = K - du, m0 = K - dm - du;
-        const bool band_tile = (u0 + 255) / 256 * 256 < K || (m0 + 255) / 256 * 256 + 256 <= u0;
-        const int grouped = state != nullptr && band_tile ? 1 : 0;
-        hipLaunchKernelGGL((transform_kernel<2, 4, 1, 4>), dim3(ncol), dim3(kThreads), 0, st, X, state, P, M, K, dm,
-                           du, grouped, Xp);
-        return hipGetLastError();
-    }
+    if (transform_split_faster(M, K)) return launch_transform_split(X, state, P, M, K, dm, du, Xp, st);
     // The pipelined kernel addresses X with 32-bit buffer offsets, so a call whose
     // X exceeds 2 GiB runs as independent chunks of rows (rows never interact).
     const int Mc = (int)(((size_t)0x7fffffff / ((size_t)K * 2)) / 128 * 128);
