@@ -10,21 +10,14 @@
 // stored as fp16 (one round-to-nearest-even from fp64) in the layout the TAC
 // kernels read, tac_M [C/g][g][g] (row r, column c) and tac_d [C].
 //
-// Two kernels, all arithmetic in fp64:
-//  * tac_stats_kernel: the data-parallel part.  A workgroup takes a span of
-//    channels (whole blocks, at least 64 channels so rows are read in 128-byte
-//    runs) and a chunk of tokens, stages 32 tokens at a time in LDS as fp64,
-//    and accumulates every (r, c) product of its blocks and every channel sum
-//    in registers, in token order.  Partial sums per chunk go to the
-//    workspace.
-//  * tac_finalize_kernel: one workgroup per block.  Adds the chunk partials in
-//    chunk order, forms the statistics, and runs the closed form: symmetric
-//    eigendecompositions by cyclic Jacobi with the round-robin (parallel)
-//    ordering, and the singular value decomposition of M by one-sided
-//    (Hestenes) Jacobi, whose singular values keep full relative accuracy.
-//    Matrices live in the workspace (g x g fp64, up to 128 KB each); the two
-//    a Jacobi iteration updates every round are staged in LDS for g <= 64, and
-//    for g = 128 the rotated matrix sits in LDS and the vectors in registers.
+// Three kernels, all arithmetic in fp64:
+//  * tac_stats_kernel: second moments and sums of both inputs, per chunk of
+//    tokens, on the fp64 matrix cores.
+//  * tac_power_kernel, one workgroup per block and input: adds the chunk
+//    partials in chunk order, forms the covariance and its power +1/2 or -1/2.
+//  * tac_match_kernel, one workgroup per block: the product of the powers, its
+//    singular value decomposition, smoothing, shrinkage, bias and outputs.
+// Both decompositions are one-sided (Hestenes) Jacobi, jacobi_columns below.
 // Results depend only on the inputs (every sum has a fixed order); they agree
 // with an fp64 LAPACK evaluation to rounding, not bit for bit.
 #include "sq_internal.hpp"
@@ -32,82 +25,153 @@
 namespace sq {
 namespace {
 
-constexpr int kCalThreads = 256;
-constexpr int kTileTok = 32;            // tokens staged per LDS tile
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
 constexpr int kMaxChunks = 64;
 constexpr int kChunkTok = 128;          // tokens per chunk before the caps
 constexpr double kEigFloor = 1e-12;
-constexpr int kLdsBlock = 64;          // largest g whose Jacobi matrices stay in LDS
 
 // ----------------------------------------------------------------- statistics
 
 // part layout: [pass][chunk][block][g*g second moments, then g sums]
+//
+// A workgroup takes a span of S channels (whole blocks) and a chunk of tokens,
+// stages 64 or 32 tokens at a time in LDS (the next tile's loads in flight
+// meanwhile) and multiplies 16 x 16 channel tiles with v_mfma_f64_16x16x4_f64,
+// four tokens at a time: lane l supplies z[token l / 16][channel l % 16] of
+// both tiles, so the only operand work is two conversions.  A block of g > 16 is
+// symmetric: only its upper tiles are computed and stored.  Blocks of g < 16
+// are read off the diagonal of one tile.
+// Bound by HBM and the fp64 matrix cores about alike at g = 16: 8192 x 4096
+// pairs are 134 MB (27 us at the copy rate) and 2.1 Gflop in whole tiles (29 us
+// at the 73 TFLOP/s the instruction reaches); 46 us.  Vector FMAs over tiles
+// staged as fp64 took 184 us, with four times the partial sums.
 template <int G>
-__global__ __launch_bounds__(kCalThreads) void tac_stats_kernel(const uint16_t* __restrict__ Zf,
-                                                               const uint16_t* __restrict__ Zq, int N, int C,
-                                                               int tok_per_chunk, int chunks,
-                                                               double* __restrict__ part) {
-    constexpr int S = G > 64 ? G : 64;                   // channels per workgroup
-    constexpr int NB = S / G;                            // blocks per workgroup
-    constexpr int P = S * G;                             // (block, r, c) products
-    constexpr int PPT = (P + kCalThreads - 1) / kCalThreads;
-    constexpr int VPT = kTileTok * S / 8 / kCalThreads;  // 16-byte loads per thread per tile
-    static_assert(VPT >= 1 && VPT * 8 * kCalThreads == kTileTok * S, "tile split");
-    __shared__ double tile[kTileTok][S + 1];
+struct StatsShape {
+    static constexpr int S = G > 64 ? G : 64;             // channels per workgroup
+    static constexpr int NT = G > 64 ? 512 : 256;         // threads
+    static constexpr int BT = G > 16 ? G / 16 : 1;        // 16-channel tiles a block spans
+    static constexpr int PER = BT * (BT + 1) / 2;         // upper tiles of a block (of one tile for g <= 16)
+    static constexpr int JOBS = S / (16 * BT) * PER;
+    static constexpr int WAVES = NT / kWave;
+    static constexpr int JPW = (JOBS + WAVES - 1) / WAVES;
+};
+constexpr int kTileTok = 64;            // tokens per tile (chunks are whole tiles)
+
+// A tile's element in LDS: blocks of g > 16 use each channel BT + 1 times, so they
+// are widened once, as they are staged.
+template <int G>
+struct StatsElem { typedef double T; };
+template <>
+struct StatsElem<1> { typedef uint16_t T; };
+template <>
+struct StatsElem<2> { typedef uint16_t T; };
+template <>
+struct StatsElem<4> { typedef uint16_t T; };
+template <>
+struct StatsElem<8> { typedef uint16_t T; };
+template <>
+struct StatsElem<16> { typedef uint16_t T; };
+__device__ __forceinline__ double widen(uint16_t h) { return (double)h2f(h); }
+__device__ __forceinline__ double widen(double v) { return v; }
+
+template <int G>
+__global__ __launch_bounds__(StatsShape<G>::NT) void tac_stats_kernel(const uint16_t* __restrict__ Zf,
+                                                                     const uint16_t* __restrict__ Zq, int N, int C,
+                                                                     int tok_per_chunk, int chunks,
+                                                                     double* __restrict__ part) {
+    using Sh = StatsShape<G>;
+    constexpr int S = Sh::S, NT = Sh::NT, JPW = Sh::JPW;
+    typedef typename StatsElem<G>::T E;
+    constexpr bool WIDE = sizeof(E) == 8;
+    constexpr int LD = S + (WIDE ? 0 : 16);              // fp16 rows: four tokens on different banks
+    constexpr int TOK = WIDE ? kTileTok / 2 : kTileTok;  // tokens staged at a time
+    constexpr int VPT = TOK * S / 8 / NT;                // 16-byte loads per thread per tile
+    static_assert(VPT * 8 * NT == TOK * S, "tile split");
+    __shared__ __attribute__((aligned(16))) E tile[TOK * LD];
 
     const int tid = threadIdx.x;
+    const int lane = tid % kWave, wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int c0 = blockIdx.x * S;
-    const int chunk = blockIdx.y;
-    const int pass = blockIdx.z;
+    const int chunk = blockIdx.y, pass = blockIdx.z;
     const uint16_t* Z = pass == 0 ? Zf : Zq;
     const int t0 = chunk * tok_per_chunk;
     const int t1 = min(N, t0 + tok_per_chunk);
+    const int il = lane % 16, kl = lane / 16;
 
-    double acc[PPT];
-    int pr[PPT], pc[PPT];
+    int ta[JPW], tb[JPW];                                // channel tiles of this wave's jobs
 #pragma unroll
-    for (int k = 0; k < PPT; ++k) {
-        acc[k] = 0.0;
-        const int p = tid + k * kCalThreads;
-        const int bs = p / (G * G), rc = p % (G * G);
-        pr[k] = p < P ? bs * G + rc / G : 0;              // span-local channel of row r
-        pc[k] = p < P ? bs * G + rc % G : 0;              // and of column c
+    for (int w = 0; w < JPW; ++w) {
+        const int job = wave + w * Sh::WAVES;
+        int u = job % Sh::PER, a = 0;
+        while (u >= Sh::BT - a) u -= Sh::BT - a, ++a;    // u-th upper tile of the block: row a, column a + u
+        const int base = job / Sh::PER * Sh::BT;
+        ta[w] = base + a;
+        tb[w] = base + a + u;
     }
-    double sum = 0.0;                                     // channel tid's sum (tid < S)
 
-    for (int tb = t0; tb < t1; tb += kTileTok) {
+    uint4 raw[VPT];
+    auto fetch = [&](int tb0) {
 #pragma unroll
         for (int v = 0; v < VPT; ++v) {
-            const int e = (tid + v * kCalThreads) * 8;    // element index in the tile
-            const int tt = e / S, ch = e % S;
-            const int t = tb + tt;
-            uint4 raw = make_uint4(0, 0, 0, 0);           // tokens past t1 contribute zeros
-            if (t < t1) raw = *reinterpret_cast<const uint4*>(Z + (size_t)t * C + c0 + ch);
-            const uint16_t* h = reinterpret_cast<const uint16_t*>(&raw);
+            const int e = (tid + v * NT) * 8;
+            const int t = tb0 + e / S;
+            raw[v] = make_uint4(0, 0, 0, 0);             // tokens past t1 contribute zeros
+            if (t < t1) raw[v] = *reinterpret_cast<const uint4*>(Z + (size_t)t * C + c0 + e % S);
+        }
+    };
+    f64x4 acc[JPW];
+    double sum[JPW];
 #pragma unroll
-            for (int q = 0; q < 8; ++q) tile[tt][ch + q] = (double)h2f(h[q]);
+    for (int w = 0; w < JPW; ++w) acc[w] = f64x4{0.0, 0.0, 0.0, 0.0}, sum[w] = 0.0;
+
+    fetch(t0);
+    for (int tk = t0; tk < t1; tk += TOK) {
+#pragma unroll
+        for (int v = 0; v < VPT; ++v) {
+            const int e = (tid + v * NT) * 8;
+            E* dst = tile + e / S * LD + e % S;
+            if constexpr (WIDE) {
+                const uint16_t* h = reinterpret_cast<const uint16_t*>(&raw[v]);
+#pragma unroll
+                for (int q = 0; q < 8; ++q) dst[q] = widen(h[q]);
+            } else {
+                *reinterpret_cast<uint4*>(dst) = raw[v];
+            }
         }
         __syncthreads();
-        const int nt = min(kTileTok, t1 - tb);
-        for (int tt = 0; tt < nt; ++tt) {
+        if (tk + TOK < t1) fetch(tk + TOK);
+#pragma unroll 4
+        for (int k = 0; k < TOK; k += 4) {
+            const E* row = tile + (k + kl) * LD + il;
 #pragma unroll
-            for (int k = 0; k < PPT; ++k) acc[k] = fma(tile[tt][pr[k]], tile[tt][pc[k]], acc[k]);
-            if (tid < S) sum += tile[tt][tid];
+            for (int w = 0; w < JPW; ++w) {
+                if (JPW * Sh::WAVES > Sh::JOBS && wave + w * Sh::WAVES >= Sh::JOBS) break;
+                const double a = widen(row[16 * ta[w]]);
+                const double b = Sh::BT == 1 ? a : widen(row[16 * tb[w]]);
+                acc[w] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc[w], 0, 0, 0);
+                sum[w] += a;
+            }
         }
         __syncthreads();
     }
-    const int B = C / G;
     const size_t stride = (size_t)G * G + G;
-    double* base = part + ((size_t)pass * chunks + chunk) * B * stride;
+    double* base = part + ((size_t)pass * chunks + chunk) * (C / G) * stride;
 #pragma unroll
-    for (int k = 0; k < PPT; ++k) {
-        const int p = tid + k * kCalThreads;
-        if (p < P) {
-            const int bs = p / (G * G), rc = p % (G * G);
-            base[(size_t)(blockIdx.x * NB + bs) * stride + rc] = acc[k];
+    for (int w = 0; w < JPW; ++w) {
+        if (wave + w * Sh::WAVES >= Sh::JOBS) break;
+        const int ca = c0 + 16 * ta[w], cb = c0 + 16 * tb[w];   // first channels of the two tiles
+        const int col = cb + il;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {                    // result register v: row 4 v + l / 16, column l % 16
+            const int row = ca + 4 * v + kl;
+            if (row / G == col / G) base[(size_t)(row / G) * stride + row % G * G + col % G] = acc[w][v];
         }
+        double t = sum[w];                               // the four token slots of a channel
+        t += __shfl_xor(t, 16);
+        t += __shfl_xor(t, 32);
+        if (ta[w] == tb[w] && kl == 0) base[(size_t)(col / G) * stride + (size_t)G * G + col % G] = t;
     }
-    if (tid < S) base[(size_t)(blockIdx.x * NB + tid / G) * stride + G * G + tid % G] = sum;
 }
 
 // ----------------------------------------------------------------- closed form
@@ -144,541 +208,434 @@ __device__ uint16_t f64_to_f16(double x) {
     return sign | (uint16_t)q;                            // q == 1024 is the smallest normal
 }
 
-__device__ int rr_player(int i, int r, int n) { return i == 0 ? 0 : 1 + (i - 1 + r) % (n - 1); }
+// Threads of the closed-form kernels: LPP lanes per pair of columns, each with
+// RPT rows.
+template <int G>
+struct SolveShape {
+    static constexpr int LPP = G >= 32 ? 16 : (G >= 8 ? 8 : G);
+    static constexpr int RPT = G / LPP;
+    static constexpr int H = G / 2;                       // pairs per round
+    static constexpr int NT = H * LPP < kWave ? kWave : H * LPP;
+    static constexpr bool VREG = G > 64;                  // V in registers: W alone fills the LDS
+    static constexpr int LDS_POWER = (VREG ? 1 : 2) * G * G * 8;
+    static constexpr int LDS_MATCH = (VREG ? 1 : 3) * G * G * 8;   // and M_final
+};
 
-// Round-robin pair t of round r over n = g players (g even), p < q.
-__device__ void rr_pair(int t, int r, int n, int& p, int& q) {
-    const int a = rr_player(t, r, n), b = rr_player(n - 1 - t, r, n);
-    p = a < b ? a : b;
-    q = a < b ? b : a;
-}
-
-// Sum over the workgroup (fixed tree order).
-__device__ double wg_sum(double v, double* red) {
-    const int tid = threadIdx.x;
-    red[tid] = v;
-    __syncthreads();
-    for (int s = kCalThreads / 2; s > 0; s >>= 1) {
-        if (tid < s) red[tid] += red[tid + s];
+// Orders this workgroup's LDS accesses.  One wave's are performed in order, so
+// there only the compiler has to keep them so.
+template <int NT>
+__device__ __forceinline__ void sync() {
+    if (NT > kWave) {
         __syncthreads();
-    }
-    const double r = red[0];
-    __syncthreads();
-    return r;
-}
-
-// Symmetric eigendecomposition of A (overwritten; eigenvalues end on its
-// diagonal), eigenvectors into the columns of V: cyclic Jacobi, round-robin.
-__device__ void jacobi_eigh(double* A, double* V, int g, double* cs, double* red) {
-    const int tid = threadIdx.x;
-    for (int e = tid; e < g * g; e += kCalThreads) V[e] = (e / g == e % g) ? 1.0 : 0.0;
-    __syncthreads();
-    if (g == 1) return;
-    const int h = g / 2;
-    for (int sweep = 0; sweep < 60; ++sweep) {
-        double off = 0.0, tot = 0.0;
-        for (int e = tid; e < g * g; e += kCalThreads) {
-            const double a2 = A[e] * A[e];
-            tot += a2;
-            if (e / g != e % g) off += a2;
-        }
-        off = wg_sum(off, red);
-        tot = wg_sum(tot, red);
-        if (!(off > 1e-30 * tot)) break;                  // also stops on a zero matrix
-        for (int r = 0; r < g - 1; ++r) {
-            if (tid < h) {
-                int p, q;
-                rr_pair(tid, r, g, p, q);
-                const double apq = A[p * g + q];
-                double c = 1.0, s = 0.0;
-                if (apq != 0.0) {
-                    const double tau = (A[q * g + q] - A[p * g + p]) / (2.0 * apq);
-                    // for |tau| beyond 1e150, tau^2 would overflow; t = 1 / (2 tau) there
-                    const double t = fabs(tau) > 1e150 ? 0.5 / tau
-                                                       : (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-                    c = 1.0 / sqrt(1.0 + t * t);
-                    s = t * c;
-                }
-                cs[2 * tid] = c;
-                cs[2 * tid + 1] = s;
-            }
-            __syncthreads();
-            for (int e = tid; e < g * h; e += kCalThreads) {      // columns: A J and V J
-                const int i = e / h, t = e % h;
-                int p, q;
-                rr_pair(t, r, g, p, q);
-                const double c = cs[2 * t], s = cs[2 * t + 1];
-                const double ap = A[i * g + p], aq = A[i * g + q];
-                A[i * g + p] = c * ap - s * aq;
-                A[i * g + q] = s * ap + c * aq;
-                const double vp = V[i * g + p], vq = V[i * g + q];
-                V[i * g + p] = c * vp - s * vq;
-                V[i * g + q] = s * vp + c * vq;
-            }
-            __syncthreads();
-            for (int e = tid; e < g * h; e += kCalThreads) {      // rows: J^T (A J)
-                const int j = e / h, t = e % h;
-                int p, q;
-                rr_pair(t, r, g, p, q);
-                const double c = cs[2 * t], s = cs[2 * t + 1];
-                const double ap = A[p * g + j], aq = A[q * g + j];
-                A[p * g + j] = c * ap - s * aq;
-                A[q * g + j] = s * ap + c * aq;
-            }
-            __syncthreads();
-        }
+    } else {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_wave_barrier();
     }
 }
 
-// R = V diag(max(l_i, 1e-12)^p) V^T for p = +1/2 or -1/2; l_i on the diagonal of D.
-__device__ void eig_power(const double* D, const double* V, double* R, int g, bool inverse, double* w) {
-    const int tid = threadIdx.x;
-    for (int k = tid; k < g; k += kCalThreads) {
-        const double l = fmax(D[k * g + k], kEigFloor);
-        w[k] = inverse ? 1.0 / sqrt(l) : sqrt(l);
-    }
-    __syncthreads();
-    for (int e = tid; e < g * g; e += kCalThreads) {
-        const int r = e / g, c = e % g;
-        double s = 0.0;
-        for (int k = 0; k < g; ++k) s = fma(V[r * g + k] * w[k], V[c * g + k], s);
-        R[e] = s;
-    }
-    __syncthreads();
-}
-
-// Singular value decomposition of G (g x g) by one-sided Jacobi: on return the
-// columns of G are u_j sigma_j and V holds the right singular vectors.
-__device__ void jacobi_svd(double* G, double* V, int g, double* cs, int* flag) {
-    const int tid = threadIdx.x;
-    for (int e = tid; e < g * g; e += kCalThreads) V[e] = (e / g == e % g) ? 1.0 : 0.0;
-    __syncthreads();
-    if (g == 1) return;
-    const int h = g / 2;
-    for (int sweep = 0; sweep < 60; ++sweep) {
-        if (tid == 0) *flag = 0;
-        __syncthreads();
-        for (int r = 0; r < g - 1; ++r) {
-            if (tid < h) {
-                int p, q;
-                rr_pair(tid, r, g, p, q);
-                double al = 0.0, be = 0.0, ga = 0.0;
-                for (int i = 0; i < g; ++i) {
-                    const double x = G[i * g + p], y = G[i * g + q];
-                    al = fma(x, x, al);
-                    be = fma(y, y, be);
-                    ga = fma(x, y, ga);
-                }
-                double c = 1.0, s = 0.0;
-                if (ga != 0.0 && fabs(ga) > 1e-15 * sqrt(al * be)) {
-                    const double zeta = (be - al) / (2.0 * ga);
-                    const double t = fabs(zeta) > 1e150
-                                         ? 0.5 / zeta
-                                         : (zeta >= 0.0 ? 1.0 : -1.0) / (fabs(zeta) + sqrt(1.0 + zeta * zeta));
-                    c = 1.0 / sqrt(1.0 + t * t);
-                    s = t * c;
-                    *flag = 1;
-                }
-                cs[2 * tid] = c;
-                cs[2 * tid + 1] = s;
-            }
-            __syncthreads();
-            for (int e = tid; e < g * h; e += kCalThreads) {
-                const int i = e / h, t = e % h;
-                int p, q;
-                rr_pair(t, r, g, p, q);
-                const double c = cs[2 * t], s = cs[2 * t + 1];
-                const double gp = G[i * g + p], gq = G[i * g + q];
-                G[i * g + p] = c * gp - s * gq;
-                G[i * g + q] = s * gp + c * gq;
-                const double vp = V[i * g + p], vq = V[i * g + q];
-                V[i * g + p] = c * vp - s * vq;
-                V[i * g + q] = s * vp + c * vq;
-            }
-            __syncthreads();
-        }
-        if (*flag == 0) break;
-        __syncthreads();
-    }
-}
-
-// g = 128: two g x g fp64 matrices (256 KB) do not fit in LDS together, and
-// updating them in global memory made every round a chain of dependent memory
-// round trips.  The matrix the rotations act on two-sidedly (A) or whose
-// columns they combine (G) stays in LDS; the vector matrix V lives in registers,
-// each row split over a lane pair: lane 2 i + h holds half h of row i.  V's
-// columns are kept in round-robin *position* order (position k holds column
-// rr_player(k, r)), half 0 holding positions 0 .. g/2 - 1 at index k and half 1
-// positions g - 1 .. g/2 at index k (position g - 1 - k), so that every round's
-// pair t (positions t and g - 1 - t) sits at index t in both lanes and all
-// register indices are static.  Between rounds positions 1 .. g - 1 shift
-// cyclically by one.  After a whole sweep (g - 1 rounds) position order is
-// column order again, and the sweep loops only stop at sweep boundaries.
-// Rotations and sums are those of jacobi_eigh and jacobi_svd; only where the
-// data lives differs (and, for the SVD, the column sums are split four ways and
-// added in a fixed order).
-constexpr int kRegBlock = 128;
-
-// The value held by the other lane of this lane's pair (lanes 2 i, 2 i + 1).
-__device__ __forceinline__ double pair_swap(double x) {
+// The value of the lane that a DPP control selects.
+template <int CTRL>
+__device__ __forceinline__ double dpp(double x) {
     const unsigned long long u = (unsigned long long)__double_as_longlong(x);
-    const int lo = __builtin_amdgcn_mov_dpp((int)(unsigned)u, 0xB1, 0xF, 0xF, false);   // quad_perm [1, 0, 3, 2]
-    const int hi = __builtin_amdgcn_mov_dpp((int)(unsigned)(u >> 32), 0xB1, 0xF, 0xF, false);
+    const int lo = __builtin_amdgcn_mov_dpp((int)(unsigned)u, CTRL, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(unsigned)(u >> 32), CTRL, 0xF, 0xF, true);
     return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
 }
 
-// Half h of row i of the identity, in position order at the start of a sweep.
-template <int G>
-__device__ __forceinline__ void half_identity(double (&v)[G / 2], int i, bool h1) {
-#pragma unroll
-    for (int k = 0; k < G / 2; ++k) v[k] = (h1 ? G - 1 - k : k) == i ? 1.0 : 0.0;
+// Sum over L consecutive lanes (L a power of two up to 16, aligned), in every lane.
+template <int L>
+__device__ __forceinline__ double lanes_sum(double x) {
+    if (L >= 2) x += dpp<0xB1>(x);                        // quad_perm [1, 0, 3, 2]
+    if (L >= 4) x += dpp<0x4E>(x);                        // quad_perm [2, 3, 0, 1]
+    if (L >= 8) x += dpp<0x141>(x);                       // row_half_mirror: the other quad of eight
+    if (L >= 16) x += dpp<0x140>(x);                      // row_mirror: the other eight of sixteen
+    return x;
 }
 
-template <int G>
-__device__ __forceinline__ void store_half(const double (&v)[G / 2], double* Vout, int i, bool h1) {
-#pragma unroll
-    for (int k = 0; k < G / 2; ++k) Vout[i * G + (h1 ? G - 1 - k : k)] = v[k];
+// 1 / sqrt(a) to working precision for a in [1, 2]: v_rsq_f64 (4e-8 off) and two
+// Newton steps.  (One third-order step is shorter, but c^2 + s^2 then drifts over
+// the rotations: 3.8e-15 against 1.5e-15 from LAPACK at G = 16, 4.1e-14 against
+// 3.9e-15 at 128.)
+__device__ __forceinline__ double rsqrt_full(double a) {
+    double y = __builtin_amdgcn_rsq(a);
+    y = y * fma(-0.5 * a * y, y, 1.5);
+    return y * fma(-0.5 * a * y, y, 1.5);
 }
 
-// One round on the lane pair's row: pair t holds columns (a, b) = (rr_player(t),
-// rr_player(g - 1 - t)); with p = min(a, b) the rotation is (v_p, v_q) <- (c v_p
-// - s v_q, s v_p + c v_q), the same map on (v_a, v_b) with s negated when a > b;
-// sg[t] holds that signed s.  Then the shift to the next round's positions.
-template <int G>
-__device__ __forceinline__ void rotate_pairs(double (&v)[G / 2], bool h1, const double* cs, const double* sg) {
-    constexpr int H = G / 2, CH = 8;
-    static_assert(H % CH == 0, "chunks of pairs");
-    // chunks of pairs, so that the rotation parameters are read as they are used
-    // and do not all sit in registers at once
-#pragma unroll
-    for (int t0 = 0; t0 < H; t0 += CH) {
-#pragma unroll
-        for (int t = t0; t < t0 + CH; ++t) {
-            const double c = cs[2 * t], sp = sg[t];
-            const double mine = v[t], other = pair_swap(mine);
-            v[t] = h1 ? sp * other + c * mine : c * mine - sp * other;
-        }
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    // half 0 moves down one index and takes position g/2 from its partner's
-    // last index; half 1 moves up one index and takes position 1 from its
-    // partner's index 1; position 0 stays.  In place, in ascending index order,
-    // carrying the old value of the previous index for half 1.
-    const double from_hi = pair_swap(v[H - 1]), from_lo = pair_swap(v[1]);
-    double prev = v[0];
-    v[0] = h1 ? from_lo : v[0];
-#pragma unroll
-    for (int k = 1; k < H - 1; ++k) {
-        const double cur = v[k];
-        v[k] = h1 ? prev : v[k + 1];
-        prev = cur;
-    }
-    v[H - 1] = h1 ? prev : from_hi;
+// The rotation (x, y) <- (c x - s y, s x + c y) that makes columns of squared
+// norms al, be and product ga orthogonal: t = sign(z) / (|z| + sqrt(1 + z^2)),
+// z = (be - al) / (2 ga), c = 1 / sqrt(1 + t^2), s = t c.  c and s must be
+// orthonormal to working precision; t only decides how much of ga the rotation
+// removes, so it is formed with the hardware's approximate reciprocal and
+// reciprocal square root (a relative 1e-7 of ga is left, which the next sweep
+// takes).
+__device__ __forceinline__ void rotation(double al, double be, double ga, double& c, double& s) {
+    const double z = (be - al) * __builtin_amdgcn_rcp(2.0 * ga);
+    const double h = fma(z, z, 1.0);
+    double t = __builtin_amdgcn_rcp(fabs(z) + h * __builtin_amdgcn_rsq(h));
+    t = fabs(z) < 1e100 ? copysign(t, z) : 0.5 * __builtin_amdgcn_rcp(z);   // z^2 would overflow
+    t = ga * ga > 1e-32 * al * be ? t : 0.0;              // orthogonal already (or a zero column)
+    c = rsqrt_full(fma(t, t, 1.0));
+    s = t * c;
 }
 
-// Symmetric eigendecomposition, A in LDS (eigenvalues end on its diagonal),
-// eigenvectors into the columns of Vout (global), V by lane-pair rows as above.  One two-sided update per
-// round over 2 x 2 blocks: block (t1, t2) takes rows (p1, q1) and columns (p2,
-// q2), rotated first by columns (A J) then by rows (J^T), the order and
-// arithmetic of jacobi_eigh's two passes.
+// One-sided (Hestenes) Jacobi on the G columns of W in LDS (column j at j G):
+// on return W holds A V for the A it came with, its columns orthogonal, and V
+// (LDS, the same layout) the accumulated rotations.  For a general A that is
+// U Sigma and the right singular vectors; for a symmetric positive semidefinite
+// A the columns are l_j v_j, V its eigenvectors.
+//
+// A round works on G / 2 disjoint pairs (round-robin ordering), LPP lanes each:
+// a lane reads its rows of both columns, the three products meet over the lanes
+// by DPP, every lane forms the rotation itself and writes its rows back, so a
+// round is one LDS round trip and one barrier (none up to G = 16, where a wave
+// holds all pairs).  Sweeps end after one that met no pair of columns farther
+// than 2e-9 from orthogonal: convergence is quadratic, so the sweep itself took
+// those to working precision.
+// Bound by the latency of a round (0.4 us at G = 16: one wave per block and
+// little more than one chain of dependent fp64 instructions).  The two-sided
+// form for the eigendecompositions took three passes over LDS and three
+// barriers a round, with the rotations formed by a few threads by full-precision
+// divides and square roots: the closed form of 256 blocks of 16 took 417 us, now
+// 91; of 32 blocks of 128, 26 ms, now 4.2.
 template <int G>
-__device__ __forceinline__ void jacobi_eigh_reg(double* A, double* Vout, double* cs, double* sg, int* pq, double* red) {
-    constexpr int H = G / 2;
-    static_assert(2 * G <= kCalThreads, "a lane pair per row");
+__device__ __forceinline__ void jacobi_columns(double* W, double* V, int* flag) {
+    using Sh = SolveShape<G>;
+    constexpr int NT = Sh::NT, LPP = Sh::LPP, RPT = Sh::RPT, H = Sh::H;
     const int tid = threadIdx.x;
-    const int row = tid / 2;
-    const bool h1 = tid & 1;
-    double v[H];
-    half_identity<G>(v, row, h1);
+    for (int e = tid; e < G * G; e += NT) V[e] = e / G == e % G ? 1.0 : 0.0;
+    sync<NT>();
+    if (G == 1) return;
+    const int t = tid / LPP, j = tid % LPP;
+    const bool on = t < H;                                // G < 16 leaves lanes of the wave idle
     for (int sweep = 0; sweep < 60; ++sweep) {
-        double off = 0.0, tot = 0.0;
-        for (int e = tid; e < G * G; e += kCalThreads) {
-            const double a2 = A[e] * A[e];
-            tot += a2;
-            if (e / G != e % G) off += a2;
-        }
-        off = wg_sum(off, red);
-        tot = wg_sum(tot, red);
-        if (!(off > 1e-30 * tot)) break;                  // also stops on a zero matrix
+        if (tid == 0) *flag = 0;
+        sync<NT>();
+        bool far = false;
+        int a = t, b = G - 1 - t;                         // players of positions t and G - 1 - t in round 0
         for (int r = 0; r < G - 1; ++r) {
-            if (tid < H) {
-                int p, q;
-                rr_pair(tid, r, G, p, q);
-                const double apq = A[p * G + q];
-                double c = 1.0, s = 0.0;
-                if (apq != 0.0) {
-                    const double tau = (A[q * G + q] - A[p * G + p]) / (2.0 * apq);
-                    const double t = fabs(tau) > 1e150 ? 0.5 / tau
-                                                       : (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-                    c = 1.0 / sqrt(1.0 + t * t);
-                    s = t * c;
+            if (on) {
+                const int p = a < b ? a : b, q = a < b ? b : a;
+                double x[RPT], y[RPT], vx[RPT], vy[RPT];
+#pragma unroll
+                for (int k = 0; k < RPT; ++k) x[k] = W[p * G + j + LPP * k], y[k] = W[q * G + j + LPP * k];
+#pragma unroll
+                for (int k = 0; k < RPT; ++k) vx[k] = V[p * G + j + LPP * k], vy[k] = V[q * G + j + LPP * k];
+                double al = 0.0, be = 0.0, ga = 0.0;
+#pragma unroll
+                for (int k = 0; k < RPT; ++k) {
+                    al = fma(x[k], x[k], al);
+                    be = fma(y[k], y[k], be);
+                    ga = fma(x[k], y[k], ga);
                 }
-                cs[2 * tid] = c;
-                cs[2 * tid + 1] = s;
-                sg[tid] = rr_player(tid, r, G) == p ? s : -s;
-                pq[2 * tid] = p;
-                pq[2 * tid + 1] = q;
+                al = lanes_sum<LPP>(al), be = lanes_sum<LPP>(be), ga = lanes_sum<LPP>(ga);
+                double c, s;
+                rotation(al, be, ga, c, s);
+                far |= ga * ga > 4e-18 * al * be;
+#pragma unroll
+                for (int k = 0; k < RPT; ++k) {
+                    W[p * G + j + LPP * k] = fma(c, x[k], -s * y[k]);
+                    W[q * G + j + LPP * k] = fma(c, y[k], s * x[k]);
+                    V[p * G + j + LPP * k] = fma(c, vx[k], -s * vy[k]);
+                    V[q * G + j + LPP * k] = fma(c, vy[k], s * vx[k]);
+                }
             }
-            __syncthreads();
-#pragma unroll 2
-            for (int blk = tid; blk < H * H; blk += kCalThreads) {
-                const int t1 = blk / H, t2 = blk % H;
-                const int p1 = pq[2 * t1], q1 = pq[2 * t1 + 1], p2 = pq[2 * t2], q2 = pq[2 * t2 + 1];
-                const double c1 = cs[2 * t1], s1 = cs[2 * t1 + 1], c2 = cs[2 * t2], s2 = cs[2 * t2 + 1];
-                const double a00 = A[p1 * G + p2], a01 = A[p1 * G + q2], a10 = A[q1 * G + p2], a11 = A[q1 * G + q2];
-                const double b00 = c2 * a00 - s2 * a01, b01 = s2 * a00 + c2 * a01;   // columns: A J
-                const double b10 = c2 * a10 - s2 * a11, b11 = s2 * a10 + c2 * a11;
-                A[p1 * G + p2] = c1 * b00 - s1 * b10;                                  // rows: J^T (A J)
-                A[q1 * G + p2] = s1 * b00 + c1 * b10;
-                A[p1 * G + q2] = c1 * b01 - s1 * b11;
-                A[q1 * G + q2] = s1 * b01 + c1 * b11;
-            }
-            rotate_pairs<G>(v, h1, cs, sg);
-            __syncthreads();
+            // position 0 keeps its player; the others take the next of 1 .. G - 1
+            if (t > 0) a = a == G - 1 ? 1 : a + 1;
+            b = b == G - 1 ? 1 : b + 1;
+            sync<NT>();
         }
+        if (far) *flag = 1;
+        sync<NT>();
+        const bool again = *flag != 0;
+        sync<NT>();
+        if (!again) break;
     }
-    store_half<G>(v, Vout, row, h1);
-    __syncthreads();
 }
 
-// One-sided Jacobi SVD of Gm (g x g, in LDS): on return its columns are
-// u_j sigma_j and Vout (global) holds the right singular vectors.  Each pair's
-// three column sums are split over four threads (rows i = 4 k + j ... ) and
-// added in the fixed order (s0 + s1) + (s2 + s3).
+// G = 128: W alone takes 128 KB of LDS, so V lives in registers.  Eight lanes
+// hold a row of V, lane j of them the positions of pairs 8 j .. 8 j + 7: index i
+// of `lo` is position 8 j + i, of `hi` position G - 1 - (8 j + i).  Positions hold
+// columns in round-robin order, so every round rotates lo[i] with hi[i], and
+// between rounds positions 1 .. G - 1 shift by one (the two ends of a lane's run
+// come from its neighbours).  After a sweep position order is column order
+// again.  cs[t] holds a round's rotation of pair t, s signed so that it applies
+// to (position t, position G - 1 - t).
 template <int G>
-__device__ __forceinline__ void jacobi_svd_reg(double* Gm, double* Vout, double* cs, double* sg, int* flag) {
-    constexpr int H = G / 2;
-    static_assert(4 * H <= kCalThreads && 2 * G <= kCalThreads, "four threads per pair, a lane pair per row");
+__device__ __forceinline__ void jacobi_columns_vreg(double* W, double* Vout, double2* cs, int* flag) {
+    using Sh = SolveShape<G>;
+    constexpr int LPP = Sh::LPP, RPT = Sh::RPT;
+    static_assert(Sh::NT == 8 * G && G / 16 == 8, "eight lanes per row, eight pairs each");
     const int tid = threadIdx.x;
-    const int row = tid / 2;
-    const bool h1 = tid & 1;
-    double v[H];
-    half_identity<G>(v, row, h1);
+    const int t = tid / LPP, j = tid % LPP;
+    const int row = tid / 8, vj = tid % 8;
+    double lo[8], hi[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        lo[i] = 8 * vj + i == row ? 1.0 : 0.0;
+        hi[i] = G - 1 - (8 * vj + i) == row ? 1.0 : 0.0;
+    }
+    __syncthreads();
     for (int sweep = 0; sweep < 60; ++sweep) {
         if (tid == 0) *flag = 0;
         __syncthreads();
+        bool far = false;
+        int a = t, b = G - 1 - t;
         for (int r = 0; r < G - 1; ++r) {
-            const int t = tid / 4, j = tid % 4;
-            int p = 0, q = 1;
+            const int p = a < b ? a : b, q = a < b ? b : a;
+            double x[RPT], y[RPT];
+#pragma unroll
+            for (int k = 0; k < RPT; ++k) x[k] = W[p * G + j + LPP * k], y[k] = W[q * G + j + LPP * k];
             double al = 0.0, be = 0.0, ga = 0.0;
-            if (t < H) {
-                rr_pair(t, r, G, p, q);
-#pragma unroll 4
-                for (int i = j; i < G; i += 4) {
-                    const double x = Gm[i * G + p], y = Gm[i * G + q];
-                    al = fma(x, x, al);
-                    be = fma(y, y, be);
-                    ga = fma(x, y, ga);
-                }
+#pragma unroll
+            for (int k = 0; k < RPT; ++k) {
+                al = fma(x[k], x[k], al);
+                be = fma(y[k], y[k], be);
+                ga = fma(x[k], y[k], ga);
             }
-            // lanes 4 t .. 4 t + 3 are consecutive in one wave: (s0 + s1) + (s2 + s3)
-            al += __shfl_xor(al, 1);
-            be += __shfl_xor(be, 1);
-            ga += __shfl_xor(ga, 1);
-            al += __shfl_xor(al, 2);
-            be += __shfl_xor(be, 2);
-            ga += __shfl_xor(ga, 2);
-            if (t < H && j == 0) {
-                double c = 1.0, s = 0.0;
-                if (ga != 0.0 && fabs(ga) > 1e-15 * sqrt(al * be)) {
-                    const double zeta = (be - al) / (2.0 * ga);
-                    const double tt = fabs(zeta) > 1e150
-                                          ? 0.5 / zeta
-                                          : (zeta >= 0.0 ? 1.0 : -1.0) / (fabs(zeta) + sqrt(1.0 + zeta * zeta));
-                    c = 1.0 / sqrt(1.0 + tt * tt);
-                    s = tt * c;
-                    *flag = 1;
-                }
-                cs[2 * t] = c;
-                cs[2 * t + 1] = s;
-                sg[t] = rr_player(t, r, G) == p ? s : -s;
+            al = lanes_sum<LPP>(al), be = lanes_sum<LPP>(be), ga = lanes_sum<LPP>(ga);
+            double c, s;
+            rotation(al, be, ga, c, s);
+            far |= ga * ga > 4e-18 * al * be;
+            double2* out = cs + (r & 1) * (G / 2);        // two rounds' worth: the last round's readers may lag
+            if (j == 0) out[t % 8 * 8 + t / 8] = make_double2(c, a == p ? s : -s);
+#pragma unroll
+            for (int k = 0; k < RPT; ++k) {
+                W[p * G + j + LPP * k] = fma(c, x[k], -s * y[k]);
+                W[q * G + j + LPP * k] = fma(c, y[k], s * x[k]);
             }
+            if (t > 0) a = a == G - 1 ? 1 : a + 1;
+            b = b == G - 1 ? 1 : b + 1;
             __syncthreads();
-#pragma unroll 2
-            for (int e = tid; e < G * H; e += kCalThreads) {
-                const int i = e / H, tt = e % H;
-                int pp, qq;
-                rr_pair(tt, r, G, pp, qq);
-                const double c = cs[2 * tt], s = cs[2 * tt + 1];
-                const double gp = Gm[i * G + pp], gq = Gm[i * G + qq];
-                Gm[i * G + pp] = c * gp - s * gq;
-                Gm[i * G + qq] = s * gp + c * gq;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const double2 f = out[8 * i + vj];
+                const double u = lo[i], w = hi[i];
+                lo[i] = fma(f.x, u, -f.y * w);
+                hi[i] = fma(f.x, w, f.y * u);
             }
-            rotate_pairs<G>(v, h1, cs, sg);
-            __syncthreads();
+            // position k takes position k + 1 (1 <= k < G - 1), position G - 1 takes 1, 0 stays
+            const double from_next = dpp<0x101>(lo[0]);           // row_shl:1: position 8 (vj + 1)
+            const double from_prev = dpp<0x111>(hi[7]);           // row_shr:1: position G - 8 vj
+            const double first = lo[1];                           // position 1 in lane 0
+            const double last_lo = vj == 7 ? hi[7] : from_next;   // lane 7: position 64 follows 63
+#pragma unroll
+            for (int i = 0; i < 7; ++i)
+                if (i > 0 || vj > 0) lo[i] = lo[i + 1];
+            lo[7] = last_lo;
+#pragma unroll
+            for (int i = 7; i > 0; --i) hi[i] = hi[i - 1];
+            hi[0] = vj == 0 ? first : from_prev;
         }
-        if (*flag == 0) break;
+        if (far) *flag = 1;
         __syncthreads();
+        const bool again = *flag != 0;
+        __syncthreads();
+        if (!again) break;
     }
-    store_half<G>(v, Vout, row, h1);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        Vout[(8 * vj + i) * G + row] = lo[i];
+        Vout[(G - 1 - (8 * vj + i)) * G + row] = hi[i];
+    }
     __syncthreads();
 }
 
-// REG: g = 128, the Jacobi matrix in LDS and V in registers (see jacobi_eigh_reg);
-// otherwise both Jacobi matrices in LDS for g <= 64, in the workspace above.
-template <bool REG>
-__global__ __launch_bounds__(kCalThreads) void tac_finalize_kernel(const double* __restrict__ part, int chunks,
-                                                                  int N, int C, int g, double rho, double eps,
-                                                                  double eta, double alpha, double* __restrict__ wk,
-                                                                  uint16_t* __restrict__ tac_M,
-                                                                  uint16_t* __restrict__ tac_d,
-                                                                  double* __restrict__ M64, double* __restrict__ d64) {
-    __shared__ double red[kCalThreads];
-    __shared__ double cs[128];
-    __shared__ double w[128];
-    __shared__ double sg[64];
-    __shared__ int pq[128];
-    __shared__ int flag;
-    extern __shared__ double lds_mats[];               // 2 g^2 doubles when g <= 64, g^2 for REG
+// out(i, j, sum_k fa(i, k) fb(k, j)) for a G x G product: 16 x 16 tiles on the
+// fp64 matrix cores (k in ascending groups of four), plain sums below 16.
+template <int G, int NT, typename FA, typename FB, typename OUT>
+__device__ __forceinline__ void product(FA fa, FB fb, OUT out) {
     const int tid = threadIdx.x;
-    const int b = blockIdx.x;
-    const int B = C / g;
-    const size_t gg = (size_t)g * g;
-    // the Jacobi iterations touch their two matrices every round: in LDS when
-    // they fit, else in the workspace
-    const bool local = !REG && g <= kLdsBlock;
-    auto stage_in = [&](const double* src) {
-        for (int e = tid; e < (int)gg; e += kCalThreads) lds_mats[e] = src[e];
-        __syncthreads();
-    };
-    auto stage_out = [&](double* a, double* v) {
-        for (int e = tid; e < (int)gg; e += kCalThreads) {
-            a[e] = lds_mats[e];
-            v[e] = lds_mats[gg + e];
+    if constexpr (G >= 16) {
+        constexpr int T = G / 16;
+        const int lane = tid % kWave, il = lane % 16, kl = lane / 16;
+        for (int u = tid / kWave; u < T * T; u += NT / kWave) {
+            const int i0 = u / T * 16, j0 = u % T * 16;
+            f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+            for (int k = 0; k < G; k += 4)
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(fa(i0 + il, k + kl), fb(k + kl, j0 + il), acc, 0, 0, 0);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) out(i0 + 4 * v + kl, j0 + il, acc[v]);
         }
-        __syncthreads();
-    };
-    auto stage_out_a = [&](double* a) {               // REG: V was written by the solver
-        for (int e = tid; e < (int)gg; e += kCalThreads) a[e] = lds_mats[e];
-        __syncthreads();
-    };
-    double* base = wk + (size_t)b * (6 * gg + 3 * g);
-    double* Sf = base;                 // Sigma_fp, then its eigenvalues
-    double* Sq = base + gg;            // Sigma_q + lambda I, then its eigenvalues
-    double* V = base + 2 * gg;         // eigenvectors / right singular vectors
-    double* R1 = base + 3 * gg;        // Sigma_fp^(1/2), later M_sv
-    double* R2 = base + 4 * gg;        // (Sigma_q + lambda I)^(-1/2)
-    double* G = base + 5 * gg;         // M, then U diag(sigma)
-    double* mu_f = base + 6 * gg;
-    double* mu_q = mu_f + g;
-    double* sig = mu_q + g;
-    const size_t stride = gg + g;
+    } else {
+        for (int e = tid; e < G * G; e += NT) {
+            double s = 0.0;
+            for (int k = 0; k < G; ++k) s = fma(fa(e / G, k), fb(k, e % G), s);
+            out(e / G, e % G, s);
+        }
+    }
+}
 
-    // statistics: chunk partials added in chunk order
-    for (int e = tid; e < (int)stride; e += kCalThreads) {
-        double sf = 0.0, sq = 0.0;
-        for (int k = 0; k < chunks; ++k) {
-            sf += part[((size_t)k * B + b) * stride + e];
-            sq += part[((size_t)(chunks + k) * B + b) * stride + e];
-        }
-        if (e < (int)gg) {
-            Sf[e] = sf / (double)N;
-            Sq[e] = sq / (double)N;
-        } else {
-            mu_f[e - gg] = sf / (double)N;
-            mu_q[e - gg] = sq / (double)N;
-        }
-    }
-    __syncthreads();
-    for (int e = tid; e < (int)gg; e += kCalThreads) {
-        const int r = e / g, c = e % g;
-        Sf[e] = Sf[e] - mu_f[r] * mu_f[c];
-        Sq[e] = Sq[e] - mu_q[r] * mu_q[c];
-    }
-    __syncthreads();
-    // damping
-    double tr = 0.0;
-    for (int k = tid; k < g; k += kCalThreads) tr += Sq[k * g + k];
-    tr = wg_sum(tr, red);
-    const double lam = rho * fmax(tr / g, eps);
-    for (int k = tid; k < g; k += kCalThreads) Sq[k * g + k] += lam;
-    __syncthreads();
-    // covariance matching
-    if (REG) {
-        stage_in(Sf);
-        jacobi_eigh_reg<kRegBlock>(lds_mats, V, cs, sg, pq, red);
-        stage_out_a(Sf);
-    } else if (local) {
-        stage_in(Sf);
-        jacobi_eigh(lds_mats, lds_mats + gg, g, cs, red);
-        stage_out(Sf, V);
-    } else {
-        jacobi_eigh(Sf, V, g, cs, red);
-    }
-    eig_power(Sf, V, R1, g, false, w);
-    if (REG) {
-        stage_in(Sq);
-        jacobi_eigh_reg<kRegBlock>(lds_mats, V, cs, sg, pq, red);
-        stage_out_a(Sq);
-    } else if (local) {
-        stage_in(Sq);
-        jacobi_eigh(lds_mats, lds_mats + gg, g, cs, red);
-        stage_out(Sq, V);
-    } else {
-        jacobi_eigh(Sq, V, g, cs, red);
-    }
-    eig_power(Sq, V, R2, g, true, w);
-    for (int e = tid; e < (int)gg; e += kCalThreads) {
-        const int r = e / g, c = e % g;
+// out(j, sum_i f(j, i)) for every column j: up to 16 lanes per column, each over
+// its rows in ascending order, added in a fixed order.
+template <int G, int NT, typename F, typename OUT>
+__device__ __forceinline__ void column_sums(F f, OUT out) {
+    constexpr int L = G < 16 ? G : 16;                    // lanes per column
+    for (int e = threadIdx.x; e < (G * L + NT - 1) / NT * NT; e += NT) {
+        const int j = e / L < G ? e / L : G - 1, l = e % L;
         double s = 0.0;
-        for (int k = 0; k < g; ++k) s = fma(R1[r * g + k], R2[k * g + c], s);
-        G[e] = s;
+        for (int i = l; i < G; i += L) s += f(j, i);
+        s = lanes_sum<L>(s);
+        if (l == 0 && e < G * L) out(j, s);
     }
-    __syncthreads();
-    // singular value smoothing
-    if (REG) {
-        stage_in(G);
-        jacobi_svd_reg<kRegBlock>(lds_mats, V, cs, sg, &flag);
-        stage_out_a(G);
-    } else if (local) {
-        stage_in(G);
-        jacobi_svd(lds_mats, lds_mats + gg, g, cs, &flag);
-        stage_out(G, V);
-    } else {
-        jacobi_svd(G, V, g, cs, &flag);
-    }
-    for (int j = tid; j < g; j += kCalThreads) {
+}
+
+// Scratch of a block: the powers of the two covariances (G x G each), for G = 128
+// the vectors of each pass's decomposition and M_final, and the means.
+template <int G>
+__device__ __forceinline__ double* block_scratch(double* wk, int b) {
+    return wk + (size_t)b * (6 * G * G + 3 * G);
+}
+
+// (Sigma_fp)^(1/2) (pass 0) or (Sigma_q + lambda I)^(-1/2) (pass 1) of block
+// blockIdx.x: one-sided Jacobi of the covariance, l_j = v_j . (A v_j).
+template <int G>
+__global__ __launch_bounds__(SolveShape<G>::NT) void tac_power_kernel(const double* __restrict__ part, int chunks,
+                                                                     int N, int C, double rho, double eps,
+                                                                     double* __restrict__ wk) {
+    using Sh = SolveShape<G>;
+    constexpr int NT = Sh::NT, GG = G * G;
+    extern __shared__ __attribute__((aligned(16))) double mats[];
+    __shared__ double mu[G], w[G];
+    __shared__ double2 cs[Sh::VREG ? G : 1];
+    __shared__ int flag;
+    double* W = mats;
+    const int tid = threadIdx.x, b = blockIdx.x, pass = blockIdx.y;
+    const size_t stride = GG + G;
+    const double* p0 = part + ((size_t)pass * chunks * (C / G) + b) * stride;
+    const size_t step = (size_t)(C / G) * stride;         // one chunk
+    double* base = block_scratch<G>(wk, b);
+    double* R = base + pass * GG;
+    double* Vg = base + (2 + pass) * GG;
+    double* V = Sh::VREG ? Vg : mats + GG;
+
+    auto chunk_sum = [&](int e) {
         double s = 0.0;
-        for (int i = 0; i < g; ++i) s = fma(G[i * g + j], G[i * g + j], s);
-        sig[j] = sqrt(s);
+#pragma unroll 8
+        for (int k = 0; k < chunks; ++k) s += p0[k * step + e];
+        return s / (double)N;
+    };
+    for (int e = tid; e < G; e += NT) {
+        mu[e] = chunk_sum(GG + e);
+        base[6 * GG + pass * G + e] = mu[e];
     }
-    __syncthreads();
-    double ssum = 0.0;
-    for (int j = tid; j < g; j += kCalThreads) ssum += sig[j];
-    const double sbar = wg_sum(ssum, red) / g;
-    for (int j = tid; j < g; j += kCalThreads) {      // factor sigma'_j / sigma_j on column j of U Sigma
+    sync<NT>();
+#pragma unroll 1
+    for (int e = tid; e < GG; e += NT) {                  // upper tiles; the lower ones are their mirror
+        const int r = e / G, c = e % G;
+        if (r / 16 > c / 16) continue;
+        const double v = chunk_sum(e) - mu[r] * mu[c];
+        W[c * G + r] = v;
+        if (r / 16 < c / 16) W[r * G + c] = v;
+    }
+    sync<NT>();
+    if (pass == 1) {                                      // damping
+        double tr = 0.0;
+        for (int k = 0; k < G; ++k) tr += W[k * G + k];
+        sync<NT>();
+        const double lam = rho * fmax(tr / G, eps);
+        for (int k = tid; k < G; k += NT) W[k * G + k] += lam;
+        sync<NT>();
+    }
+    if constexpr (Sh::VREG)
+        jacobi_columns_vreg<G>(W, V, cs, &flag);
+    else
+        jacobi_columns<G>(W, V, &flag);
+    column_sums<G, NT>([&](int j, int i) { return V[j * G + i] * W[j * G + i]; },
+                       [&](int j, double l) {
+                           l = fmax(l, kEigFloor);
+                           w[j] = pass == 1 ? 1.0 / sqrt(l) : sqrt(l);
+                       });
+    sync<NT>();
+    if constexpr (Sh::VREG) {                             // the vectors into LDS, in place of W
+        for (int e = tid; e < GG; e += NT) W[e] = V[e];
+        V = W;
+        __syncthreads();
+    }
+    product<G, NT>([&](int i, int k) { return V[k * G + i] * w[k]; }, [&](int k, int j) { return V[k * G + j]; },
+                   [&](int i, int j, double s) { R[j * G + i] = s; });
+}
+
+// Covariance matching, singular value smoothing, shrinkage and bias of block
+// blockIdx.x from the two powers and means.
+template <int G>
+__global__ __launch_bounds__(SolveShape<G>::NT) void tac_match_kernel(double* __restrict__ wk, double eta,
+                                                                     double alpha, uint16_t* __restrict__ tac_M,
+                                                                     uint16_t* __restrict__ tac_d,
+                                                                     double* __restrict__ M64,
+                                                                     double* __restrict__ d64) {
+    using Sh = SolveShape<G>;
+    constexpr int NT = Sh::NT, GG = G * G;
+    extern __shared__ __attribute__((aligned(16))) double mats[];
+    __shared__ double sig[G], w[G], muq[G];
+    __shared__ double2 cs[Sh::VREG ? G : 1];
+    __shared__ int flag;
+    double* W = mats;
+    const int tid = threadIdx.x, b = blockIdx.x;
+    double* base = block_scratch<G>(wk, b);
+    const double* R1 = base;
+    const double* R2 = base + GG;
+    double* V = Sh::VREG ? base + 2 * GG : mats + GG;
+    const double* mu = base + 6 * GG;
+    for (int e = tid; e < G; e += NT) muq[e] = mu[G + e];
+    product<G, NT>([&](int i, int k) { return R1[k * G + i]; }, [&](int k, int j) { return R2[j * G + k]; },
+                   [&](int i, int j, double s) { W[j * G + i] = s; });
+    sync<NT>();
+    if constexpr (Sh::VREG)
+        jacobi_columns_vreg<G>(W, V, cs, &flag);
+    else
+        jacobi_columns<G>(W, V, &flag);
+    column_sums<G, NT>([&](int j, int i) { return W[j * G + i] * W[j * G + i]; },
+                       [&](int j, double s) { sig[j] = sqrt(s); });
+    sync<NT>();
+    double sbar = 0.0;
+    for (int k = 0; k < G; ++k) sbar += sig[k];
+    sbar /= G;
+    for (int j = tid; j < G; j += NT) {                   // factor sigma'_j / sigma_j on column j of U Sigma
         const double s = sig[j];
         w[j] = s > 0.0 ? ((1.0 - eta) * s + eta * sbar) / s : 0.0;
     }
-    __syncthreads();
-    for (int e = tid; e < (int)gg; e += kCalThreads) {
-        const int r = e / g, c = e % g;
-        double s = 0.0;
-        for (int k = 0; k < g; ++k) s = fma(G[r * g + k] * w[k], V[c * g + k], s);
-        // identity shrinkage
-        R1[e] = (1.0 - alpha) * s + (r == c ? alpha : 0.0);
+    sync<NT>();
+    double* Mf = Sh::VREG ? base + 4 * GG : mats + 2 * GG;   // M_final, with the identity shrinkage
+    product<G, NT>([&](int i, int k) { return W[k * G + i] * w[k]; }, [&](int k, int j) { return V[k * G + j]; },
+                   [&](int i, int j, double s) { Mf[i * G + j] = (1.0 - alpha) * s + (i == j ? alpha : 0.0); });
+    sync<NT>();
+    for (int e = tid; e < GG; e += NT) {
+        tac_M[(size_t)b * GG + e] = f64_to_f16(Mf[e]);
+        if (M64) M64[(size_t)b * GG + e] = Mf[e];
     }
-    __syncthreads();
-    // bias, outputs
-    for (int r = tid; r < g; r += kCalThreads) {
+    for (int r = tid; r < G; r += NT) {                   // bias
         double s = 0.0;
-        for (int c = 0; c < g; ++c) s = fma(R1[r * g + c], mu_q[c], s);
-        const double d = mu_f[r] - s;
-        tac_d[b * g + r] = f64_to_f16(d);
-        if (d64) d64[b * g + r] = d;
-    }
-    for (int e = tid; e < (int)gg; e += kCalThreads) {
-        tac_M[(size_t)b * gg + e] = f64_to_f16(R1[e]);
-        if (M64) M64[(size_t)b * gg + e] = R1[e];
+        for (int c = 0; c < G; ++c) s = fma(Mf[r * G + c], muq[c], s);
+        const double d = mu[r] - s;
+        tac_d[b * G + r] = f64_to_f16(d);
+        if (d64) d64[b * G + r] = d;
     }
 }
 
 template <int G>
-hipError_t launch_stats(const uint16_t* Zf, const uint16_t* Zq, int N, int C, int per, int chunks, double* part,
-                        hipStream_t st) {
-    constexpr int S = G > 64 ? G : 64;
-    dim3 grid(C / S, chunks, 2);
-    hipLaunchKernelGGL(tac_stats_kernel<G>, grid, dim3(kCalThreads), 0, st, Zf, Zq, N, C, per, chunks, part);
+hipError_t launch_calib(const uint16_t* Zf, const uint16_t* Zq, int N, int C, int per, int chunks, double* part,
+                        double rho, double eps, double eta, double alpha, double* wk, uint16_t* tac_M,
+                        uint16_t* tac_d, double* M64, double* d64, hipStream_t st) {
+    using St = StatsShape<G>;
+    using Sh = SolveShape<G>;
+    static std::atomic<int> power_set[kMaxDevices], match_set[kMaxDevices];
+    hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&tac_power_kernel<G>), Sh::LDS_POWER, power_set);
+    if (e != hipSuccess) return e;
+    e = allow_dynamic_lds(reinterpret_cast<const void*>(&tac_match_kernel<G>), Sh::LDS_MATCH, match_set);
+    if (e != hipSuccess) return e;
+    const unsigned B = (unsigned)(C / G);
+    hipLaunchKernelGGL(tac_stats_kernel<G>, dim3(C / St::S, chunks, 2), dim3(St::NT), 0, st, Zf, Zq, N, C, per,
+                       chunks, part);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(tac_power_kernel<G>, dim3(B, 2), dim3(Sh::NT), Sh::LDS_POWER, st, part, chunks, N, C, rho,
+                       eps, wk);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(tac_match_kernel<G>, dim3(B), dim3(Sh::NT), Sh::LDS_MATCH, st, wk, eta, alpha, tac_M, tac_d,
+                       M64, d64);
     return hipGetLastError();
 }
 
@@ -692,6 +649,20 @@ void calib_plan(int N, int C, int g, int& chunks, int& per) {
     chunks = (N + kChunkTok - 1) / kChunkTok;
     chunks = chunks < 1 ? 1 : (chunks > cap ? cap : chunks);
     per = (N + chunks - 1) / chunks;
+    chunks = (N + per - 1) / per;
+}
+
+
+// The chunks that are run: as many as give about 2048 workgroups (eight per CU),
+// whole tiles of tokens each, within the workspace's number.  More only add
+// partial sums to write and read (64 chunks of 8192 x 4096 at g = 16: 142 MB of
+// them against 134 MB of input).
+void calib_chunks(int N, int C, int g, int& chunks, int& per) {
+    calib_plan(N, C, g, chunks, per);
+    const int spans = C / (g > 64 ? g : 64);
+    const int want = (1024 + spans - 1) / spans;
+    if (chunks > want) chunks = want;
+    per = ((N + chunks - 1) / chunks + kTileTok - 1) / kTileTok * kTileTok;
     chunks = (N + per - 1) / per;
 }
 
@@ -711,36 +682,24 @@ hipError_t launch_tac_calib(const uint16_t* Zf, const uint16_t* Zq, int N, int C
                             double eta, double alpha, uint16_t* tac_M, uint16_t* tac_d, double* M64, double* d64,
                             void* ws, hipStream_t st) {
     int chunks, per;
-    calib_plan(N, C, g, chunks, per);
+    calib_chunks(N, C, g, chunks, per);
     const size_t B = (size_t)C / g, gg = (size_t)g * g;
     double* part = static_cast<double*>(ws);
     const size_t part_bytes = 2 * (size_t)chunks * B * (gg + g) * sizeof(double);
     double* wk = reinterpret_cast<double*>(static_cast<uint8_t*>(ws) + ((part_bytes + 255) / 256) * 256);
-    hipError_t e;
+    auto run = [&](auto launch) {
+        return launch(Zf, Zq, N, C, per, chunks, part, rho, eps, eta, alpha, wk, tac_M, tac_d, M64, d64, st);
+    };
     switch (g) {
-        case 1: e = launch_stats<1>(Zf, Zq, N, C, per, chunks, part, st); break;
-        case 2: e = launch_stats<2>(Zf, Zq, N, C, per, chunks, part, st); break;
-        case 4: e = launch_stats<4>(Zf, Zq, N, C, per, chunks, part, st); break;
-        case 8: e = launch_stats<8>(Zf, Zq, N, C, per, chunks, part, st); break;
-        case 16: e = launch_stats<16>(Zf, Zq, N, C, per, chunks, part, st); break;
-        case 32: e = launch_stats<32>(Zf, Zq, N, C, per, chunks, part, st); break;
-        case 64: e = launch_stats<64>(Zf, Zq, N, C, per, chunks, part, st); break;
-        default: e = launch_stats<128>(Zf, Zq, N, C, per, chunks, part, st); break;
+        case 1: return run(launch_calib<1>);
+        case 2: return run(launch_calib<2>);
+        case 4: return run(launch_calib<4>);
+        case 8: return run(launch_calib<8>);
+        case 16: return run(launch_calib<16>);
+        case 32: return run(launch_calib<32>);
+        case 64: return run(launch_calib<64>);
+        default: return run(launch_calib<128>);
     }
-    if (e != hipSuccess) return e;
-    if (g == kRegBlock) {
-        static std::atomic<int> lds_set[kMaxDevices];   // above the 64 KB default for dynamic LDS
-        const hipError_t attr = allow_dynamic_lds(reinterpret_cast<const void*>(&tac_finalize_kernel<true>),
-                                                  (int)(gg * sizeof(double)), lds_set);
-        if (attr != hipSuccess) return attr;
-        hipLaunchKernelGGL(tac_finalize_kernel<true>, dim3((unsigned)B), dim3(kCalThreads), gg * sizeof(double), st,
-                           part, chunks, N, C, g, rho, eps, eta, alpha, wk, tac_M, tac_d, M64, d64);
-        return hipGetLastError();
-    }
-    const size_t lds = g <= kLdsBlock ? 2 * gg * sizeof(double) : 0;
-    hipLaunchKernelGGL(tac_finalize_kernel<false>, dim3((unsigned)B), dim3(kCalThreads), lds, st, part, chunks, N, C,
-                       g, rho, eps, eta, alpha, wk, tac_M, tac_d, M64, d64);
-    return hipGetLastError();
 }
 
 }  // namespace sq
