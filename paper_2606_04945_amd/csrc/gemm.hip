@@ -210,6 +210,9 @@ __global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_
     // one per 16 x 16 block.  Below K = 131072 the scaled sum 256 x dot cannot
     // wrap, so the shift alone recovers the dot product (acc_value's special
     // case is only needed at the largest K).
+    // k groups: block (i, j) of a wave is added up and stored by one of the groups
+    // (4-10 % of a call of a few microseconds against group 0 doing it all)
+    auto owns = [&](int i, int j) { return KG == 1 || (i * TN + j) % KG == kg; };
     auto epilogue = [&](auto NOWRAP) {
         float sa[TM];
         float4 sw[TN];
@@ -228,7 +231,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
                 const int col = col0 + (wn * TN + j) * 16 + lg * 4;   // N % 8 == 0: all four in range or none
-                if (col >= N) continue;
+                if (col >= N || !owns(i, j)) continue;
                 const int v0 = value(acc[i][j][0]), v1 = value(acc[i][j][1]);
                 const int v2 = value(acc[i][j][2]), v3 = value(acc[i][j][3]);
                 if (SPLIT) {
@@ -255,10 +258,11 @@ __global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_
             wait_vm<LA + LB>();                          // this wave's loads of step kt are done
         else
             wait_vm<0>();
-        // ... and every wave's.  A bare s_barrier: the workgroup fence of
-        // __syncthreads would also wait for the loads still in flight, which
-        // is the overlap this pipeline exists for.
-        __builtin_amdgcn_s_barrier();
+        // ... and every wave's (a k group of one wave reads only what it loaded
+        // itself).  A bare s_barrier: the workgroup fence of __syncthreads would
+        // also wait for the loads still in flight, which is the overlap this
+        // pipeline exists for.
+        if (NW > 1) __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         frags(sm + sc * SB + kg * SG);
         if (kt + 2 < kt1) issue(kt + 2, sn);             // into the stage step kt - 1 used
@@ -272,23 +276,30 @@ __global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_
         if (kt + 2 < kt1) step(kt + 2, 2, 1);
     }
     if constexpr (KG > 1) {
-        // every wave is past its last fragment read: the stages take the partial sums
+        // every wave is past its last fragment read: the stages take the partial
+        // sums, and each group adds up the blocks it owns
         __syncthreads();
-        v4i* red = reinterpret_cast<v4i*>(sm);           // [KG - 1][NW][TM][TN][lane]
-        if (kg > 0) {
+        v4i* red = reinterpret_cast<v4i*>(sm);           // [KG - 1: the groups but the owner][NW][TM][TN][lane]
+        auto slot = [&](int g, int i, int j) {
+            const int owner = (i * TN + j) % KG;
+            return ((((g < owner ? g : g - 1) * NW + wave) * TM + i) * TN + j) * kWave + lane;
+        };
 #pragma unroll
-            for (int i = 0; i < TM; ++i)
+        for (int i = 0; i < TM; ++i)
 #pragma unroll
-                for (int j = 0; j < TN; ++j) red[((((kg - 1) * NW + wave) * TM + i) * TN + j) * kWave + lane] = acc[i][j];
-        }
+            for (int j = 0; j < TN; ++j)
+                if (!owns(i, j)) red[slot(kg, i, j)] = acc[i][j];
         __syncthreads();
-        if (kg > 0) return;
+        if (kg >= TM * TN) return;
 #pragma unroll
-        for (int g = 0; g < KG - 1; ++g)
+        for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int i = 0; i < TM; ++i)
+            for (int j = 0; j < TN; ++j) {
+                if (!owns(i, j)) continue;
 #pragma unroll
-                for (int j = 0; j < TN; ++j) acc[i][j] += red[(((g * NW + wave) * TM + i) * TN + j) * kWave + lane];
+                for (int g = 0; g < KG; ++g)
+                    if (g != kg) acc[i][j] += red[slot(g, i, j)];
+            }
     }
     if (K < 131072)
         epilogue(std::true_type{});
@@ -695,6 +706,7 @@ __global__ __launch_bounds__(256) void splitk_epilogue(const int32_t* __restrict
 struct Plan {
     int cfg;       // 0: 256 x 128, 1: 128 x 128, 2: 64 x 64, 4: 64 x 128, 7: 128 x 256 (8-bit), 8: 128 x 128
                    // in two waves of 128 x 64 (8-bit), 9: 128 x 128 in two k groups of four waves,
+                   // 10 ... 14: small grids in k groups (see choose_k_groups),
                    // 3: short M, K split in the
                    // workgroup, 5: short M, activations shared in LDS (see launch_gemm), 6: short M on
                    // fragment-ordered weights (see launch_gemm_frag)
@@ -839,9 +851,6 @@ hipError_t launch_short_frag_bits(const Plan& p, const uint8_t* Aq, const float*
         case 1: return launch_short_frag_tm<1, BITS>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, st);
         case 2: return launch_short_frag_tm<2, BITS>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, st);
         case 3: return launch_short_frag_tm<3, BITS>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, st);
-        case 4:   // four row tiles only for 4-bit codes (frag_four_tiles)
-            if constexpr (BITS == 4) return launch_short_frag_tm<4, BITS>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, st);
-            return hipErrorInvalidConfiguration;
         default: return hipErrorInvalidConfiguration;
     }
 }
@@ -851,15 +860,6 @@ hipError_t launch_short_frag(const Plan& p, const uint8_t* Aq, const float* s_a,
     return bits == 8 ? launch_short_frag_bits<8>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, st)
                      : launch_short_frag_bits<4>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, st);
 }
-
-// Fragment-ordered weights at 49 ... 64 tokens: the short-M kernel with four
-// row tiles where it beats the tiled plan (its K split and separate reduction),
-// measured at 64 tokens: layers up to 12288 wide with K <= 4096 (LLaDA QKV 15.9
-// -> 12.8 us, O 10.2 -> 8.5; Dream QKV 10.5 -> 10.0, O 9.8 -> 8.0).  Wider or
-// deeper layers stay tiled (gate+up 17.1 against 19.3 us, down 14.9 against
-// 17.6): there each wave's expansion of four activation fragments per weight
-// fragment costs more than the tiled plan loses.
-bool frag_four_tiles(int M, int N, int K) { return M > 48 && M <= 64 && N <= 12288 && K <= 4096; }
 
 template <int TM, int BITS>
 hipError_t skinny_kw_tm(int kw, const uint8_t* Aq, const float* s_a, const uint8_t* Wq, const float* s_w, int M, int N,
@@ -896,6 +896,48 @@ hipError_t finish_split(const Plan& p, int32_t* part, const float* s_a, const fl
     return hipGetLastError();
 }
 
+// Small grids: tiles so small that a launch of the whole shape is at most one
+// workgroup per CU, and as many k groups as their stages fit LDS, so that a CU
+// still has 8 ... 16 waves and K needs no split across workgroups (its partial
+// sums through HBM and the second launch cost about 4 us).  A few hundred tokens
+// are bound by the latency of the k steps, not by operands or MFMAs: the time
+// follows the number of steps a wave takes, so the smallest tile that still
+// fits one round wins, for 4-bit and 8-bit codes alike (65 shapes, 50 ... 2000
+// rows, N = 512 ... 37888, K = 1024 ... 32768, against every tile below and the
+// former plans).  4-bit, former plan -> k groups: 50 x 4096 x 4096 7.7 -> 5.2 us
+// (32 x 32 tiles), 64 x 12288 x 4096 12.6 -> 9.7 (64 x 64), 128 x 4096 x 12288
+// 17.5 -> 14.0 (32 x 64), 250 x 4096 x 12288 25.9 -> 18.5 (64 x 64), 250 x 3584
+// x 18944 37.1 -> 25.7, 512 x 4096 x 12288 37.9 -> 29.1 (64 x 128); 8-bit: 250 x
+// 4096 x 4096 21.8 -> 12.6, 512 x 3584 x 18944 92 -> 68.
+// Where they stand back, with the former plan's times:
+//  - 32 x 32 tiles re-read the operands most; many tiles of a deep K are then
+//    bound by it: 8-bit 64 x 4096 x 12288 (256 tiles, 192 k steps) 20.5 against
+//    18.7 us, 4-bit 250 x 512 x 32768 (128 tiles, 256) 16.8 against 15.8, while
+//    8-bit 50 x 1536 x 12288 (96, 192) takes 16.1 against 17.0;
+//  - 4-bit 64 x 128 tiles of a shallow K on three quarters of the CUs or less:
+//    200 x 4608 x 3584 (144 tiles) 11.7 against 11.3.
+Plan choose_k_groups(int M, int N, int K, int bits) {
+    const int nk = (K * bits / 8 + kKB - 1) / kKB;
+    auto tiles = [&](int bm, int bn) { return (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+    Plan none = make_plan(M, N, K, 64, 64, 1, bits);
+    const struct {
+        int cfg, bm, bn;
+    } shapes[] = {{10, 32, 32}, {11, 32, 64}, {12, 64, 64}, {13, 64, 128}};
+    for (const auto& s : shapes) {
+        const long t = tiles(s.bm, s.bn);
+        if (t > 256) continue;
+        if (s.cfg == 10 && nk >= 160 && t * nk >= 32768) return none;
+        const bool deep = nk >= 64;
+        if (s.cfg == 13 && bits == 4 && !deep && t < 192) return none;
+        Plan p = make_plan(M, N, K, s.bm, s.bn, 1, bits);
+        // deep K: three k groups of four 64 x 32 waves (512 x 4096 x 12288 29.1
+        // us) for two of four 32 x 64 (31.0; 64 x 24576 x 4096 15.3 against 14.6)
+        p.cfg = s.cfg == 13 && deep ? 14 : s.cfg;
+        return p;
+    }
+    return none;
+}
+
 // The production plan (from measured sweeps on MI355X, graph-replayed with
 // rotating weights):
 //  - M <= 48: the short-M kernels (weight streaming; activations shared in LDS
@@ -910,14 +952,21 @@ hipError_t finish_split(const Plan& p, int32_t* part, const float* s_a, const fl
 //    tiles; else 128 x 128 in two waves of 128 x 64 from 640 of its tiles
 //    (three workgroups per CU fill the chip at 768); else 128 x 256 from 192
 //    of its tiles; else 128 x 128 (four waves) from 192 of its tiles;
-//  - 129 ... 256 tiles of 128 x 128 and at least 128 k steps (64 for 8-bit
+//  - at most 256 tiles of 32 x 32, 32 x 64, 64 x 64 or 64 x 128: the smallest
+//    of these, in k groups (choose_k_groups);
+//  - 129 ... 256 tiles of 128 x 128 and at least 128 k steps (48 for 8-bit
 //    codes): 128 x 128 with two k groups of four waves (see below);
 //  - at least 512 tiles of 64 x 128: 64 x 128 (four waves of 64 x 32);
-//  - otherwise 64 x 64 (four waves of 32 x 32), with K split below 256 tiles
-//    (twice as deep for K >= 8192) and kept at 8 k steps or more per split.
-Plan choose_plan(int M, int N, int K, int bits) {
+//  - otherwise 64 x 64 (four waves of 32 x 32); with few tiles (only where the
+//    k groups stand back, see choose_k_groups) split over K across workgroups,
+//    twice as deep for K >= 8192 and kept at 8 k steps or more per split.
+Plan choose_plan(int M, int N, int K, int bits, bool k_groups = true) {
     const int nk = (K * bits / 8 + kKB - 1) / kKB;
     auto tiles = [&](int bm, int bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+    if (M > 16 * kShortMaxTiles && k_groups) {
+        const Plan p = choose_k_groups(M, N, K, bits);
+        if (p.cfg >= 0) return p;
+    }
     auto splits_for = [&](int t) {
         int s = t >= 256 ? 1 : (256 + t - 1) / t;
         if (K >= 8192 && t <= 256) s *= 2;
@@ -945,13 +994,15 @@ Plan choose_plan(int M, int N, int K, int bits) {
             p.cfg = 3;
             p.waves = kw;
         }
-    } else if (tiles(128, 128) > 128 && tiles(128, 128) <= 256 && nk >= (bits == 8 ? 64 : 128)) {
+    } else if (tiles(128, 128) > 128 && tiles(128, 128) <= 256 && nk >= (bits == 8 ? (k_groups ? 48 : 64) : 128)) {
         // at most one 128 x 128 tile per CU and a deep K: two k groups of four
         // waves per tile (interleaved timings with rotating weights against the
         // plans below: 8-bit 1024 x 4096 x 4096 13 % faster, 1024 x 4096 x 12288
         // 15 %, 256 x 12288 x 4096 9 %, 1024 x 3584 x 18944 18 %; 4-bit
         // 1024 x 3584 x 18944 17 %, but 4 % slower at 1024 x 4096 x 12288 (96
-        // k steps) and 6 % at 768 x 4096 x 12288, hence 128 k steps for 4-bit)
+        // k steps) and 6 % at 768 x 4096 x 12288, hence 128 k steps for 4-bit;
+        // 8-bit at 56 k steps: 512 x 4608 x 3584 27.2 -> 23.1 us, 1000 x 3584 x
+        // 3584 25.5 -> 22.3)
         p = make_plan(M, N, K, 128, 128, 1, bits);
         p.cfg = 9;
     } else if (bits == 4 && (tiles(256, 128) >= 448 || tiles(128, 128) >= 448)) {
@@ -1061,7 +1112,7 @@ hipError_t launch_weights_to_frag(const uint8_t* Wq, int N, int K, uint8_t* Wf, 
 
 hipError_t launch_gemm_frag(const uint8_t* Aq, const float* s_a, const uint8_t* Wf, const float* s_w, int M, int N,
                             int K, uint16_t* Y, int32_t* acc, void* ws, hipStream_t st, int bits) {
-    if (M <= 16 * kShortMaxTiles || (bits == 4 && frag_four_tiles(M, N, K)))
+    if (M <= 16 * kShortMaxTiles)
         return launch_short_frag(choose_frag_short(M, N, K, bits), Aq, s_a, Wf, s_w, M, N, K, Y, acc, st, bits);
     const Plan p = choose_plan(M, N, K, bits);   // the tiled plans of row-major weights
     int32_t* part = static_cast<int32_t*>(ws);
@@ -1070,6 +1121,11 @@ hipError_t launch_gemm_frag(const uint8_t* Aq, const float* s_a, const uint8_t* 
         switch (p.cfg) {
             case 7: e = launch_tiled<2, 2, 4, 8, 8, 2, true>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, part, st); break;
             case 9: e = launch_tiled<2, 2, 4, 4, 8, 2, true, 2>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, part, st); break;
+            case 10: e = launch_tiled<1, 1, 2, 2, 8, 3, true, 12>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, part, st); break;
+            case 11: e = launch_tiled<1, 2, 2, 2, 8, 4, true, 8>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, part, st); break;
+            case 12: e = launch_tiled<2, 1, 2, 4, 8, 2, true, 4>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, part, st); break;
+            case 13: e = launch_tiled<2, 2, 2, 4, 8, 2, true, 2>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, part, st); break;
+            case 14: e = launch_tiled<1, 4, 4, 2, 8, 2, true, 3>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, part, st); break;
             case 8: e = launch_tiled<1, 2, 8, 4, 8, 2, true>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, part, st); break;
             case 1: e = launch_tiled<2, 2, 4, 4, 8, 3, true>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, part, st); break;
             case 2: e = launch_tiled<2, 2, 2, 2, 8, 4, true>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, part, st); break;
@@ -1079,6 +1135,11 @@ hipError_t launch_gemm_frag(const uint8_t* Aq, const float* s_a, const uint8_t* 
         switch (p.cfg) {
             case 0: e = launch_tiled<4, 2, 4, 4, 4, 2, true>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, part, st); break;
             case 9: e = launch_tiled<2, 2, 4, 4, 4, 2, true, 2>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, part, st); break;
+            case 10: e = launch_tiled<1, 1, 2, 2, 4, 3, true, 12>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, part, st); break;
+            case 11: e = launch_tiled<1, 2, 2, 2, 4, 4, true, 8>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, part, st); break;
+            case 12: e = launch_tiled<2, 1, 2, 4, 4, 2, true, 4>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, part, st); break;
+            case 13: e = launch_tiled<2, 2, 2, 4, 4, 2, true, 2>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, part, st); break;
+            case 14: e = launch_tiled<1, 4, 4, 2, 4, 2, true, 3>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, part, st); break;
             case 1: e = launch_tiled<2, 2, 4, 4, 4, 3, true>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, part, st); break;
             case 2: e = launch_tiled<2, 2, 2, 2, 4, 4, true>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, part, st); break;
             default: e = launch_tiled<1, 4, 4, 2, 4, 4, true>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, part, st); break;
@@ -1088,8 +1149,11 @@ hipError_t launch_gemm_frag(const uint8_t* Aq, const float* s_a, const uint8_t* 
     return finish_split(p, part, s_a, s_w, M, N, Y, acc, st);
 }
 
+// What callers provide is what the K split across workgroups takes on every
+// small grid, also where k groups run in its place and leave it unused: the size
+// is part of the interface, so calls are accepted and refused by one rule.
 size_t gemm_workspace_bytes(int M, int N, int K, int bits) {
-    const Plan p = choose_plan(M, N, K, bits);
+    const Plan p = choose_plan(M, N, K, bits, false);
     return p.splits > 1 ? (size_t)p.splits * M * N * sizeof(int32_t) : 0;
 }
 
@@ -1103,6 +1167,11 @@ hipError_t launch_gemm(const uint8_t* Aq, const float* s_a, const uint8_t* Wq, c
             case 3: e = skinny_kw<8>(p.waves, Aq, s_a, Wq, s_w, M, N, K, Y, acc, st); break;
             case 7: e = launch_tiled<2, 2, 4, 8, 8, 2>(p, Aq, s_a, Wq, s_w, M, N, K, Y, acc, part, st); break;
             case 9: e = launch_tiled<2, 2, 4, 4, 8, 2, false, 2>(p, Aq, s_a, Wq, s_w, M, N, K, Y, acc, part, st); break;
+            case 10: e = launch_tiled<1, 1, 2, 2, 8, 3, false, 12>(p, Aq, s_a, Wq, s_w, M, N, K, Y, acc, part, st); break;
+            case 11: e = launch_tiled<1, 2, 2, 2, 8, 4, false, 8>(p, Aq, s_a, Wq, s_w, M, N, K, Y, acc, part, st); break;
+            case 12: e = launch_tiled<2, 1, 2, 4, 8, 2, false, 4>(p, Aq, s_a, Wq, s_w, M, N, K, Y, acc, part, st); break;
+            case 13: e = launch_tiled<2, 2, 2, 4, 8, 2, false, 2>(p, Aq, s_a, Wq, s_w, M, N, K, Y, acc, part, st); break;
+            case 14: e = launch_tiled<1, 4, 4, 2, 8, 2, false, 3>(p, Aq, s_a, Wq, s_w, M, N, K, Y, acc, part, st); break;
             case 8: e = launch_tiled<1, 2, 8, 4, 8, 2>(p, Aq, s_a, Wq, s_w, M, N, K, Y, acc, part, st); break;
             case 1: e = launch_tiled<2, 2, 4, 4, 8, 3>(p, Aq, s_a, Wq, s_w, M, N, K, Y, acc, part, st); break;
             case 2: e = launch_tiled<2, 2, 2, 2, 8, 4>(p, Aq, s_a, Wq, s_w, M, N, K, Y, acc, part, st); break;
@@ -1114,6 +1183,11 @@ hipError_t launch_gemm(const uint8_t* Aq, const float* s_a, const uint8_t* Wq, c
             case 5: e = launch_skinny_shared(p.waves, Aq, s_a, Wq, s_w, M, N, K, Y, acc, st); break;
             case 0: e = launch_tiled<4, 2, 4, 4, 4, 2>(p, Aq, s_a, Wq, s_w, M, N, K, Y, acc, part, st); break;
             case 9: e = launch_tiled<2, 2, 4, 4, 4, 2, false, 2>(p, Aq, s_a, Wq, s_w, M, N, K, Y, acc, part, st); break;
+            case 10: e = launch_tiled<1, 1, 2, 2, 4, 3, false, 12>(p, Aq, s_a, Wq, s_w, M, N, K, Y, acc, part, st); break;
+            case 11: e = launch_tiled<1, 2, 2, 2, 4, 4, false, 8>(p, Aq, s_a, Wq, s_w, M, N, K, Y, acc, part, st); break;
+            case 12: e = launch_tiled<2, 1, 2, 4, 4, 2, false, 4>(p, Aq, s_a, Wq, s_w, M, N, K, Y, acc, part, st); break;
+            case 13: e = launch_tiled<2, 2, 2, 4, 4, 2, false, 2>(p, Aq, s_a, Wq, s_w, M, N, K, Y, acc, part, st); break;
+            case 14: e = launch_tiled<1, 4, 4, 2, 4, 2, false, 3>(p, Aq, s_a, Wq, s_w, M, N, K, Y, acc, part, st); break;
             case 1: e = launch_tiled<2, 2, 4, 4, 4, 3>(p, Aq, s_a, Wq, s_w, M, N, K, Y, acc, part, st); break;
             case 2: e = launch_tiled<2, 2, 2, 2, 4, 4>(p, Aq, s_a, Wq, s_w, M, N, K, Y, acc, part, st); break;
             default: e = launch_tiled<1, 4, 4, 2, 4, 4>(p, Aq, s_a, Wq, s_w, M, N, K, Y, acc, part, st); break;
