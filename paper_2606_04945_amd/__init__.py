@@ -37,7 +37,7 @@ def _on_stream(fn):
     @functools.wraps(fn)
     def wrapper(*args, stream=None, **kw):
         if stream is None:
-            return fn(*args, stream=None, **kw)
+            return fn(*args, **kw)
         s = stream if isinstance(stream, torch.cuda.Stream) else torch.cuda.ExternalStream(int(stream))
         with torch.cuda.stream(s):
             return fn(*args, stream=s, **kw)
@@ -48,13 +48,26 @@ def _ptr(t: Optional[torch.Tensor]):
     return None if t is None else t.data_ptr()
 
 
+# The current stream's handle without the Stream object that
+# torch.cuda.current_stream() builds (0.1 against 2.7 us of host time, in a call
+# whose launch takes 3.4); the arguments were seen to be device tensors first, so
+# the runtime is up.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream) -> int:
     if stream is None:
+        if _raw_stream is not None and _device is not None:
+            return _raw_stream(_device())
         stream = torch.cuda.current_stream()
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def _need(t: Optional[torch.Tensor], name: str, dtype, shape=None, optional=False):
+    # what holds on every good call, in one test (0.2 us); the message otherwise
+    if t is not None and t.is_cuda and t.dtype is dtype and t.is_contiguous() and (shape is None or t.shape == shape):
+        return
     if t is None:
         if optional:
             return
