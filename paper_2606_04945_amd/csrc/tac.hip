@@ -407,12 +407,22 @@ __global__ __launch_bounds__(64 * (kTqMaxConsumerWaves + 1)) void tac_quant_kern
 
     if (t < nrows) st_lds[t] = gated ? state[row_begin + t] : 0;
 
+    // row r of the run goes to slot (r + kTqRing - 1) % kTqRing: row 0 to the last
+    // one, which the parameter staging leaves alone, so it is requested first
+    auto slot = [&](int r) { return ring + (r + kTqRing - 1) % kTqRing * slot_bytes; };
+    auto issue = [&](int r) {
+        const u32x4 rz = sgpr_rsrc(Z + (size_t)(row_begin + r) * K, (uint32_t)K * 2);
+        uint8_t* dst = slot(r);
+        for (int j = 0; j < cw; ++j) dma16(rz, lds_addr(dst + j * 1024), (uint32_t)(j * kWave + lane) * 16);
+    };
+    if (producer) issue(0);
+
     // tac_M viewed as [K][G]: this thread's rows c0 .. c0 + 7 are 8 G fp16
     // values, held as G vectors of 8 (element r G + c of the run = row r,
     // column c), widened by the mixed-precision multiply-adds
     v8h mh[G];
-    float dv[8];
     const int cm = active ? c0 : 0;                     // other threads read the first rows, unused
+    const v8h draw = *reinterpret_cast<const v8h*>(d + cm);
     if constexpr (G >= 4) {
         // A thread's rows are PB = 16 G contiguous bytes at PB t, so loaded
         // directly the lanes of one 16-byte load would touch up to 64 cache
@@ -426,7 +436,7 @@ __global__ __launch_bounds__(64 * (kTqMaxConsumerWaves + 1)) void tac_quant_kern
         constexpr int TPP = G == 16 ? 16 : (G == 8 ? 32 : 64);   // at most 5 KB per wave per pass
         constexpr int PASSES = kWave / TPP;
         constexpr int LOADS = TPP * NC / kWave;         // 16-byte loads per lane per pass
-        static_assert(TPP * SLOT <= 1024 * kTqRing, "parameter staging fits in a wave's share of the ring");
+        static_assert(TPP * SLOT <= 1024 * (kTqRing - 1), "parameter staging fits in a wave's share of the ring but a slot");
         if (!producer) {
             uint8_t* stage = ring + wave * (TPP * SLOT);
             const __amdgpu_buffer_rsrc_t rM = make_rsrc(Mb, (uint32_t)K * G * 2);
@@ -436,17 +446,21 @@ __global__ __launch_bounds__(64 * (kTqMaxConsumerWaves + 1)) void tac_quant_kern
                 __builtin_amdgcn_wave_barrier();
                 __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
             };
+            // every pass's loads are requested first: one memory round trip, not
+            // one per pass
+            v4i ch[PASSES][LOADS];
 #pragma unroll
-            for (int p = 0; p < PASSES; ++p) {
-                v4i ch[LOADS];
+            for (int p = 0; p < PASSES; ++p)
 #pragma unroll
                 for (int i = 0; i < LOADS; ++i)
-                    ch[i] = __builtin_amdgcn_raw_buffer_load_b128(rM, (slab + p * TPP * NC + i * kWave + lane) * 16,
-                                                                  0, 0);
+                    ch[p][i] = __builtin_amdgcn_raw_buffer_load_b128(
+                        rM, (slab + p * TPP * NC + i * kWave + lane) * 16, 0, 0);
+#pragma unroll
+            for (int p = 0; p < PASSES; ++p) {
 #pragma unroll
                 for (int i = 0; i < LOADS; ++i) {
                     const int c = i * kWave + lane;     // chunk of this pass: thread c / NC, piece c % NC
-                    *reinterpret_cast<v4i*>(stage + (c / NC) * SLOT + (c % NC) * 16) = ch[i];
+                    *reinterpret_cast<v4i*>(stage + (c / NC) * SLOT + (c % NC) * 16) = ch[p][i];
                 }
                 wave_sync();
                 if (lane / TPP == p) {
@@ -462,18 +476,14 @@ __global__ __launch_bounds__(64 * (kTqMaxConsumerWaves + 1)) void tac_quant_kern
 #pragma unroll
         for (int j = 0; j < G; ++j) mh[j] = *reinterpret_cast<const v8h*>(Mb + (size_t)cm * G + 8 * j);
     }
+    float dv[8];
 #pragma unroll
-    for (int r = 0; r < 8; ++r) dv[r] = h2f(d[cm + r]);
+    for (int r = 0; r < 8; ++r) dv[r] = (float)draw[r];
     __syncthreads();                                    // parameters read; states in LDS; the ring is free
 
-    // producer: row r of the run into slot r % kTqRing, one 1 KB load per consumer wave
+    // producer: the rows of the run into their slots, one 1 KB load per consumer wave
     if (producer) {
-        auto issue = [&](int r) {
-            const u32x4 rz = sgpr_rsrc(Z + (size_t)(row_begin + r) * K, (uint32_t)K * 2);
-            uint8_t* dst = ring + (r % kTqRing) * slot_bytes;
-            for (int j = 0; j < cw; ++j) dma16(rz, lds_addr(dst + j * 1024), (uint32_t)(j * kWave + lane) * 16);
-        };
-        for (int r = 0; r < kTqRing - 1 && r < nrows; ++r) issue(r);
+        for (int r = 1; r < kTqRing - 1 && r < nrows; ++r) issue(r);
         for (int i = 0; i <= nrows; ++i) {
             if (i < nrows) wait_ring(min(kTqRing - 2, nrows - 1 - i) * cw);   // row i has landed
             ring_barrier();
@@ -495,7 +505,7 @@ __global__ __launch_bounds__(64 * (kTqMaxConsumerWaves + 1)) void tac_quant_kern
     auto compute = [&](int i) {                         // row i: TAC, gate, partial max
         float amax = 0.0f;
         if (active) {
-            const uint8_t* src = ring + (i % kTqRing) * slot_bytes + z0 * 2;
+            const uint8_t* src = slot(i) + z0 * 2;
             v8h zh[ZW / 8];
 #pragma unroll
             for (int v = 0; v < ZW / 8; ++v) zh[v] = *reinterpret_cast<const v8h*>(src + 16 * v);
@@ -875,8 +885,13 @@ hipError_t launch_tac_quant(const uint16_t* Z, const uint16_t* Mb, const uint16_
                          : launch_tqm<4, 32>(M, Z, Mb, d, state, K, dm, du, Aq, s, st);
     const int cw = (K / 8 + kWave - 1) / kWave;
     const int threads = (cw + 1) * kWave;
-    // about two workgroups per CU, each streaming a run of up to 64 rows
-    int rows = (M + 511) / 512;
+    // about two workgroups per CU, each streaming a run of up to 64 rows; one where
+    // a CU holds only one (g = 16 at K > 3584: nine waves of 124 registers), and up
+    // to 1024 rows at g = 16 and seven waves, where reading the block rows (16 g K
+    // bits per workgroup) weighs most: 1024 x 4096 14.1 -> 11.0 us, 2000 x 4096
+    // 20.6 -> 17.3, 700 x 3584 10.1 -> 8.9 (2000 x 3584 15.4 against 16.4)
+    const int wgs = g == 16 && (cw == 8 || (cw == 7 && M <= 1024)) ? 256 : 512;
+    int rows = (M + wgs - 1) / wgs;
     rows = rows < 1 ? 1 : (rows > kTqMaxRows ? kTqMaxRows : rows);
     const dim3 grid((M + rows - 1) / rows);
     // at most 6 x 8 KB + 128 bytes (K <= 4096): inside the default 64 KB dynamic-LDS limit
