@@ -15,11 +15,14 @@
 // codes are defined by, this one trades that for the matrix cores.
 //
 // The kernel is the GEMM's three-stage direct-to-LDS pipeline on fp16
-// operands: 128 x 128 or 64 x 64 output tiles, four waves.  A stage
-// holds one k step of 32 of x and the matching steps of both halves of Ps
-// (hi and lo), so x is fetched and read from LDS once for both: two
-// v_mfma_f32_16x16x32_f16 per 16 x 16 tile and step (hi then lo, into one
-// accumulator), the gate applied in the epilogue, fp32 out.
+// operands.  A stage holds one k step of 32 of x and the matching steps of both
+// halves of Ps (hi and lo) for each k group, so x is fetched and read from LDS
+// once for both: two v_mfma_f32_16x16x32_f16 per 16 x 16 tile and step (hi then
+// lo, into one accumulator), the gate applied in the epilogue, fp32 out.
+// What bounds it: at a thousand rows and more the fp16 matrix cores (4096 x
+// 12288: 1.15 PFLOP/s executed) and the LDS reads that feed them (a 64 x 64 wave
+// reads 12 KB per 32 MFMAs, a 128 x 64 one 16 KB per 64); below, the latency of
+// the k steps a wave takes one after another, which the k groups divide.
 #include "tile_common.hpp"
 
 namespace sq {
@@ -49,28 +52,32 @@ __global__ __launch_bounds__(256) void split_basis_kernel(const float* __restric
     }
 }
 
-template <int WM, int WN, int TM, int TN>
-__global__ __launch_bounds__(64 * WM * WN) void transform_mfma_kernel(const uint16_t* __restrict__ X,
+// KG > 1: KG sets of WM x WN waves share the tile and take turns over its k
+// steps; their sums meet in LDS.
+template <int WM, int WN, int TM, int TN, int KG>
+__global__ __launch_bounds__(64 * WM * WN * KG) void transform_mfma_kernel(const uint16_t* __restrict__ X,
                                                                      const uint8_t* __restrict__ state,
                                                                      const uint16_t* __restrict__ Ps, int M, int K,
                                                                      int dm, int du, float* __restrict__ Xp) {
     constexpr int NW = WM * WN;
     constexpr int BM = 16 * WM * TM, BN = 16 * WN * TN;
     constexpr int AB = BM * kKStep, BB = BN * kKStep;   // bytes of one stage: x, then Ps hi, then Ps lo
-    constexpr int SB = AB + 2 * BB;
+    constexpr int SG = AB + 2 * BB, SB = KG * SG;
     constexpr int LA = AB / 1024 / NW, LB = BB / 1024 / NW;
     static_assert(LA * NW * 1024 == AB && LB * NW * 1024 == BB, "stage loads must divide evenly");
-    __shared__ __attribute__((aligned(16))) uint8_t sm[3 * SB];
+    extern __shared__ __attribute__((aligned(16))) uint8_t sm[];
 
     const int tid = threadIdx.x;
-    const int lane = tid % kWave, wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int lane = tid % kWave, wave_all = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int kg = wave_all / NW, wave = wave_all % NW;
     const int wm = wave / WN, wn = wave % WN;
     int rt, ct;
     xcd_tile(blockIdx.x, (M + BM - 1) / BM, (K + BN - 1) / BN, 8, rt, ct);
     const int row0 = rt * BM, col0 = ct * BN;
     const uint32_t lda = (uint32_t)K * 2;                // X row bytes
     const uint32_t ldb = (uint32_t)K * 4;                // Ps row bytes (hi then lo)
-    const int nk = (int)(lda / kKStep);                  // k steps (each with both halves of Ps)
+    const int nk_all = (int)(lda / kKStep);              // k steps (each with both halves of Ps)
+    const int nk = (nk_all + KG - 1) / KG;               // stages: stage kt holds steps KG kt .. KG kt + KG - 1
     const uint32_t lo_off = lda;                         // byte offset of the lo half in a Ps row
     const u32x4 rA = sgpr_rsrc(X, (uint32_t)M * lda);
     const u32x4 rB = sgpr_rsrc(Ps, (uint32_t)K * ldb);
@@ -89,16 +96,18 @@ __global__ __launch_bounds__(64 * WM * WN) void transform_mfma_kernel(const uint
         const uint32_t seg = 16 * ((lane % 4) ^ swz(r));
         ob[u] = col0 + r < K ? (uint32_t)(col0 + r) * ldb + seg : kOOB;
     }
-    auto issue = [&](int kt, int stage) {
-        uint8_t* dA = sm + stage * SB;
+    auto issue = [&](int skt, int stage) {
+        const int kt = KG * skt + kg;                    // this k group's step; past the end it reads as zeros
+        const bool past = kt >= nk_all;
+        uint8_t* dA = sm + stage * SB + kg * SG;
         uint8_t* dB = dA + AB;
         const uint32_t ko = (uint32_t)kt * kKStep;
 #pragma unroll
-        for (int u = 0; u < LA; ++u) dma16(rA, lds_addr(dA + (wave * LA + u) * 1024), oa[u] == kOOB ? kOOB : oa[u] + ko);
+        for (int u = 0; u < LA; ++u) dma16(rA, lds_addr(dA + (wave * LA + u) * 1024), past || oa[u] == kOOB ? kOOB : oa[u] + ko);
 #pragma unroll
         for (int u = 0; u < LB; ++u) {
-            dma16(rB, lds_addr(dB + (wave * LB + u) * 1024), ob[u] == kOOB ? kOOB : ob[u] + ko);
-            dma16(rB, lds_addr(dB + BB + (wave * LB + u) * 1024), ob[u] == kOOB ? kOOB : ob[u] + lo_off + ko);
+            dma16(rB, lds_addr(dB + (wave * LB + u) * 1024), past || ob[u] == kOOB ? kOOB : ob[u] + ko);
+            dma16(rB, lds_addr(dB + BB + (wave * LB + u) * 1024), past || ob[u] == kOOB ? kOOB : ob[u] + lo_off + ko);
         }
     };
 
@@ -119,7 +128,7 @@ __global__ __launch_bounds__(64 * WM * WN) void transform_mfma_kernel(const uint
             wait_vm<0>();
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
-        const uint8_t* st = sm + sc * SB;
+        const uint8_t* st = sm + sc * SB + kg * SG;
         v8h fa[TM], fh[TN], fl[TN];
 #pragma unroll
         for (int i = 0; i < TM; ++i) fa[i] = *reinterpret_cast<const v8h*>(st + offA + i * 16 * kKStep);
@@ -130,12 +139,13 @@ __global__ __launch_bounds__(64 * WM * WN) void transform_mfma_kernel(const uint
         }
         if (kt + 2 < nk) issue(kt + 2, sn);
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+        for (int i = 0; i < TM; ++i) {
+            // basis columns as the row operand: see the epilogue
 #pragma unroll
-            for (int j = 0; j < TN; ++j) {   // basis columns as the row operand: see the epilogue
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fh[j], fa[i], acc[i][j], 0, 0, 0);
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fl[j], fa[i], acc[i][j], 0, 0, 0);
-            }
+            for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fh[j], fa[i], acc[i][j], 0, 0, 0);
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fl[j], fa[i], acc[i][j], 0, 0, 0);
+        }
     };
     issue(0, 0);
     if (1 < nk) issue(1, 1);
@@ -143,6 +153,34 @@ __global__ __launch_bounds__(64 * WM * WN) void transform_mfma_kernel(const uint
         step(kt, 0, 2);
         if (kt + 1 < nk) step(kt + 1, 1, 0);
         if (kt + 2 < nk) step(kt + 2, 2, 1);
+    }
+    auto owns = [&](int i, int j) { return KG == 1 || (i * TN + j) % KG == kg; };
+    if constexpr (KG > 1) {
+        // every wave is past its last fragment read: the stages take the partial
+        // sums, and each group adds up and stores the blocks it owns
+        static_assert((KG - 1) * NW * TM * TN * kWave * 16 <= 3 * SB, "k-group partial sums fit in the stages");
+        __syncthreads();
+        v4f* red = reinterpret_cast<v4f*>(sm);           // [KG - 1: the groups but the owner][NW][TM][TN][lane]
+        auto slot = [&](int g, int i, int j) {
+            const int owner = (i * TN + j) % KG;
+            return ((((g < owner ? g : g - 1) * NW + wave) * TM + i) * TN + j) * kWave + lane;
+        };
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+                if (!owns(i, j)) red[slot(kg, i, j)] = acc[i][j];
+        __syncthreads();
+        if (kg >= TM * TN) return;
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                if (!owns(i, j)) continue;
+#pragma unroll
+                for (int g = 0; g < KG; ++g)
+                    if (g != kg) acc[i][j] += red[slot(g, i, j)];
+            }
     }
     // acc[i][j]: token row lr of A block i, columns 4 lg .. 4 lg + 3 of basis block j
 #pragma unroll
@@ -153,7 +191,7 @@ __global__ __launch_bounds__(64 * WM * WN) void transform_mfma_kernel(const uint
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
             const int col = col0 + (wn * TN + j) * 16 + lg * 4;
-            if (col >= K) continue;
+            if (col >= K || !owns(i, j)) continue;
             float4 o;
             o.x = (!state || kept(col + 0, K, dm, du, masked)) ? acc[i][j][0] * kBasisUnscale : 0.0f;
             o.y = (!state || kept(col + 1, K, dm, du, masked)) ? acc[i][j][1] * kBasisUnscale : 0.0f;
@@ -171,22 +209,48 @@ hipError_t launch_split_basis(const float* P, int K, uint16_t* Ps, hipStream_t s
     return hipGetLastError();
 }
 
+namespace {
+
+template <int WM, int WN, int TM, int TN, int KG>
+hipError_t launch_mfma(const uint16_t* X, const uint8_t* state, const uint16_t* Ps, int M, int K, int dm, int du,
+                       float* Xp, hipStream_t st) {
+    constexpr int BM = 16 * WM * TM, BN = 16 * WN * TN, LDS = 3 * KG * (BM + 2 * BN) * kKStep;
+    static_assert(LDS <= 160 * 1024, "three stages fit in LDS");
+    const size_t tiles = (size_t)((M + BM - 1) / BM) * (size_t)((K + BN - 1) / BN);
+    if (tiles > 0x7fffffffu) return hipErrorInvalidConfiguration;
+    static std::atomic<int> lds_set[kMaxDevices];
+    const hipError_t attr = allow_dynamic_lds(
+        reinterpret_cast<const void*>(&transform_mfma_kernel<WM, WN, TM, TN, KG>), LDS, lds_set);
+    if (attr != hipSuccess) return attr;
+    hipLaunchKernelGGL((transform_mfma_kernel<WM, WN, TM, TN, KG>), dim3((unsigned)tiles), dim3(64 * WM * WN * KG), LDS,
+                       st, X, state, Ps, M, K, dm, du, Xp);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+// Every tile fills a CU's LDS, so a launch runs in rounds of 256 workgroups.  Up to
+// 128 x 128, the smallest tile that needs one round (rows of one launch: 64 x
+// 4096 50.8 -> 20.0 us on 32 x 32 tiles in eight k groups, 128 x 4096 49.2 ->
+// 29.8 on 32 x 64, 256 x 4096 49.4 -> 42.5 on 64 x 64, 512 x 4096 70.6 -> 49.7 on
+// 128 x 64, 1024 x 4096 81.4 -> 74.4 on 128 x 128, against 64 x 64 or 128 x 128
+// without k groups); up to 64 rows 32 x 32 whatever the grid (reading Ps bounds
+// it: 16 x 18944 272 us, 321 on 32 x 64).  Past one round, 256 x 128 (eight waves
+// of 64 x 64) takes 0.87 of the time of two 128 x 128 tiles: 4096 x 12288 2670 ->
+// 2149 us in 6 rounds, but 1024 x 12288 656 us in 2 against 629 in 3 of 128 x 128.
 hipError_t launch_transform_fast(const uint16_t* X, const uint8_t* state, const uint16_t* Ps, int M, int K, int dm,
                                  int du, float* Xp, hipStream_t st) {
-    const size_t t128 = (size_t)((M + 127) / 128) * (size_t)((K + 127) / 128);
-    const size_t t64 = (size_t)((M + 63) / 64) * (size_t)((K + 63) / 64);
-    if (t64 > 0x7fffffffu) return hipErrorInvalidConfiguration;
-    // 128 x 128 tiles from one per CU on (1024 x 4096, 256 tiles: 73.6 us
-    // against 99.8 us for 512 tiles of 64 x 128 and 111.6 us for 1024 of 64 x 64;
-    // 1024 x 12288: 580 us against 862 and 1003)
-    if (t128 >= 256) {
-        hipLaunchKernelGGL((transform_mfma_kernel<2, 2, 4, 4>), dim3((unsigned)t128), dim3(256), 0, st, X, state, Ps,
-                           M, K, dm, du, Xp);
-    } else {
-        hipLaunchKernelGGL((transform_mfma_kernel<2, 2, 2, 2>), dim3((unsigned)t64), dim3(256), 0, st, X, state, Ps,
-                           M, K, dm, du, Xp);
-    }
-    return hipGetLastError();
+    auto rounds = [&](int bm, int bn) {
+        return ((size_t)((M + bm - 1) / bm) * (size_t)((K + bn - 1) / bn) + 255) / 256;
+    };
+    if (M <= 64 || rounds(32, 32) == 1)
+        return launch_mfma<1, 1, 2, 2, 8>(X, state, Ps, M, K, dm, du, Xp, st);
+    if (rounds(32, 64) == 1) return launch_mfma<1, 2, 2, 2, 4>(X, state, Ps, M, K, dm, du, Xp, st);
+    if (rounds(64, 64) == 1) return launch_mfma<2, 2, 2, 2, 4>(X, state, Ps, M, K, dm, du, Xp, st);
+    if (rounds(128, 64) == 1) return launch_mfma<2, 2, 4, 2, 2>(X, state, Ps, M, K, dm, du, Xp, st);
+    if (rounds(128, 128) == 1 || 100 * rounds(128, 128) < 174 * rounds(256, 128))
+        return launch_mfma<1, 2, 8, 4, 2>(X, state, Ps, M, K, dm, du, Xp, st);
+    return launch_mfma<4, 2, 4, 4, 1>(X, state, Ps, M, K, dm, du, Xp, st);
 }
 
 }  // namespace sq
