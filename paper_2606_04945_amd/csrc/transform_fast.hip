@@ -19,10 +19,14 @@
 // halves of Ps (hi and lo) for each k group, so x is fetched and read from LDS
 // once for both: two v_mfma_f32_16x16x32_f16 per 16 x 16 tile and step (hi then
 // lo, into one accumulator), the gate applied in the epilogue, fp32 out.
-// What bounds it: at a thousand rows and more the fp16 matrix cores (4096 x
-// 12288: 1.15 PFLOP/s executed) and the LDS reads that feed them (a 64 x 64 wave
-// reads 12 KB per 32 MFMAs, a 128 x 64 one 16 KB per 64); below, the latency of
-// the k steps a wave takes one after another, which the k groups divide.
+// What bounds it: at a thousand rows and more the fp16 matrix cores (busy 57 % of
+// the cycles at 4096 x 12288, where the card holds 1.95 GHz; 1.24 PFLOP/s executed)
+// and the LDS reads that feed them (a 64 x 64 wave reads 12 KB per 32 MFMAs, a 128 x
+// 64 one 16 KB per 64); below, the latency of the k steps a wave takes one after
+// another, which the k groups divide.  With a step's fragment reads and copies
+// issued ahead of its MFMAs the two took turns, as one or two waves per SIMD do not
+// cover for each other: 1024 x 12288 629 -> 569 us with them spread between the
+// MFMAs, 1024 x 4096 78 -> 64, 4096 x 12288 2155 -> 1996.
 #include "tile_common.hpp"
 
 namespace sq {
@@ -55,7 +59,7 @@ __global__ __launch_bounds__(256) void split_basis_kernel(const float* __restric
 // KG > 1: KG sets of WM x WN waves share the tile and take turns over its k
 // steps; their sums meet in LDS.
 template <int WM, int WN, int TM, int TN, int KG>
-__global__ __launch_bounds__(64 * WM * WN * KG) void transform_mfma_kernel(const uint16_t* __restrict__ X,
+__global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_eu(2))) void transform_mfma_kernel(const uint16_t* __restrict__ X,
                                                                      const uint8_t* __restrict__ state,
                                                                      const uint16_t* __restrict__ Ps, int M, int K,
                                                                      int dm, int du, float* __restrict__ Xp) {
@@ -83,31 +87,35 @@ __global__ __launch_bounds__(64 * WM * WN * KG) void transform_mfma_kernel(const
     const u32x4 rB = sgpr_rsrc(Ps, (uint32_t)K * ldb);
     auto swz = [](int r) { return (r >> 1) & 3; };
 
-    uint32_t oa[LA], ob[LB];
-#pragma unroll
-    for (int u = 0; u < LA; ++u) {
-        const int r = 16 * (wave * LA + u) + lane / 4;
-        const uint32_t seg = 16 * ((lane % 4) ^ swz(r));
-        oa[u] = row0 + r < M ? (uint32_t)(row0 + r) * lda + seg : kOOB;
-    }
-#pragma unroll
-    for (int u = 0; u < LB; ++u) {
-        const int r = 16 * (wave * LB + u) + lane / 4;
-        const uint32_t seg = 16 * ((lane % 4) ^ swz(r));
-        ob[u] = col0 + r < K ? (uint32_t)(col0 + r) * ldb + seg : kOOB;
-    }
-    auto issue = [&](int skt, int stage) {
-        const int kt = KG * skt + kg;                    // this k group's step; past the end it reads as zeros
+    // this lane's segment of the wave's first rows; later copies are 16 rows on each.
+    // Rows past M (columns past K) lie past the descriptor's end and read as zeros.
+    const uint32_t seg = 16 * ((lane % 4) ^ swz(lane / 4));
+    const uint32_t oa = (uint32_t)(row0 + 16 * wave * LA + lane / 4) * lda + seg;
+    const uint32_t ob = (uint32_t)(col0 + 16 * wave * LB + lane / 4) * ldb + seg;
+    // wave-uniform, kept apart from the vector part of an address: combined, every
+    // copy's address takes a register of its own through the loop
+    auto scalar = [](uint32_t o) {
+        asm("" : "+s"(o));
+        return o;
+    };
+    // copy q of this wave's share of stage skt: x, then Ps hi and lo in turn.  Past
+    // the last step the descriptors are empty, so the copies bring zeros and every
+    // stage has the same number of copies to wait for.
+    auto copy = [&](int skt, int stage, int q) {
+        const int kt = KG * skt + kg;                    // this k group's step
         const bool past = kt >= nk_all;
-        uint8_t* dA = sm + stage * SB + kg * SG;
-        uint8_t* dB = dA + AB;
+        const uint8_t* d = sm + stage * SB + kg * SG;
         const uint32_t ko = (uint32_t)kt * kKStep;
-#pragma unroll
-        for (int u = 0; u < LA; ++u) dma16(rA, lds_addr(dA + (wave * LA + u) * 1024), past || oa[u] == kOOB ? kOOB : oa[u] + ko);
-#pragma unroll
-        for (int u = 0; u < LB; ++u) {
-            dma16(rB, lds_addr(dB + (wave * LB + u) * 1024), past || ob[u] == kOOB ? kOOB : ob[u] + ko);
-            dma16(rB, lds_addr(dB + BB + (wave * LB + u) * 1024), past || ob[u] == kOOB ? kOOB : ob[u] + lo_off + ko);
+        if (q < LA) {
+            u32x4 r = rA;
+            r[2] = past ? 0u : r[2];
+            dma16(r, lds_addr(d + (wave * LA + q) * 1024), oa + scalar(16 * q * lda + ko));
+        } else {
+            const int u = (q - LA) / 2, lo = (q - LA) % 2;
+            u32x4 r = rB;
+            r[2] = past ? 0u : r[2];
+            dma16(r, lds_addr(d + AB + lo * BB + (wave * LB + u) * 1024), 
+                  ob + scalar(16 * u * ldb + ko + (lo ? lo_off : 0)));
         }
     };
 
@@ -120,40 +128,71 @@ __global__ __launch_bounds__(64 * WM * WN * KG) void transform_mfma_kernel(const
     const int fo = (lg ^ swz(lr)) * 16;
     const int offA = ((wm * TM) * 16 + lr) * kKStep + fo;
     const int offB = AB + ((wn * TN) * 16 + lr) * kKStep + fo;
-    auto step = [&](int kt, int sc, int sn) {
-        asm volatile("" ::: "memory");
-        if (kt + 1 < nk)
-            wait_vm<LA + 2 * LB>();
+    // Fragments are read one stage ahead, and those reads and the copies of the stage
+    // after next are spread between the MFMAs: a wave that issued them all at once
+    // would wait for the queues with idle matrix cores.  The basis fragments and the
+    // last two of x have a second register set; the others of x are read again into
+    // the registers that their row of MFMAs has just used.
+    v8h fa[2][TM], fh[2][TN], fl[2][TN];
+    auto again = [](int i) { return i < TM - 2; };
+    auto frag_a = [&](const uint8_t* st, int set, int i) {
+        fa[again(i) ? 0 : set][i] = *reinterpret_cast<const v8h*>(st + offA + i * 16 * kKStep);
+    };
+    auto frag = [&](const uint8_t* st, int set, int q) {
+        if (q < TN)
+            fh[set][q] = *reinterpret_cast<const v8h*>(st + offB + q * 16 * kKStep);
+        else if (q < 2 * TN)
+            fl[set][q - TN] = *reinterpret_cast<const v8h*>(st + offB + BB + (q - TN) * 16 * kKStep);
         else
-            wait_vm<0>();
-        __builtin_amdgcn_s_barrier();
+            frag_a(st, set, TM - 1 - (q - 2 * TN));
+    };
+    constexpr int NR = 2 * TN + (TM < 2 ? TM : 2), NC = LA + 2 * LB, NX = NR + NC, NM = 2 * TM * TN;
+    // multiplies stage kt (register set `set`, LDS stage s0, which the copies of
+    // stage kt + 3 then reuse) while the fragments of stage kt + 1 come in from s1
+    auto step = [&](int kt, int set, int s0, int s1) {
         asm volatile("" ::: "memory");
-        const uint8_t* st = sm + sc * SB + kg * SG;
-        v8h fa[TM], fh[TN], fl[TN];
+        wait_vm<NC>();                                   // stage kt + 1 has landed; this wave's reads of kt are done
+        __builtin_amdgcn_s_barrier();                    // ... and every wave's
+        asm volatile("" ::: "memory");
+        const uint8_t* st = sm + s1 * SB + kg * SG;
 #pragma unroll
-        for (int i = 0; i < TM; ++i) fa[i] = *reinterpret_cast<const v8h*>(st + offA + i * 16 * kKStep);
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            fh[j] = *reinterpret_cast<const v8h*>(st + offB + j * 16 * kKStep);
-            fl[j] = *reinterpret_cast<const v8h*>(st + offB + BB + j * 16 * kKStep);
-        }
-        if (kt + 2 < nk) issue(kt + 2, sn);
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
+        for (int m = 0; m < NM; ++m) {
             // basis columns as the row operand: see the epilogue
+            const int i = m / (2 * TN), j = m % TN;
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(m / TN % 2 ? fl[set][j] : fh[set][j],
+                                                               fa[again(i) ? 0 : set][i], acc[i][j], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (again(i) && m % (2 * TN) == 2 * TN - 1) frag_a(st, set ^ 1, i);
 #pragma unroll
-            for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fh[j], fa[i], acc[i][j], 0, 0, 0);
-#pragma unroll
-            for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fl[j], fa[i], acc[i][j], 0, 0, 0);
+            for (int q = m * NX / NM; q < (m + 1) * NX / NM; ++q) {
+                if (q < NR)
+                    frag(st, set ^ 1, q);
+                else
+                    copy(kt + 3, s0, q - NR);
+            }
+            __builtin_amdgcn_sched_barrier(0);
         }
     };
-    issue(0, 0);
-    if (1 < nk) issue(1, 1);
-    for (int kt = 0; kt < nk; kt += 3) {
-        step(kt, 0, 2);
-        if (kt + 1 < nk) step(kt + 1, 1, 0);
-        if (kt + 2 < nk) step(kt + 2, 2, 1);
+#pragma unroll
+    for (int s = 0; s < 3; ++s)
+#pragma unroll
+        for (int q = 0; q < NC; ++q) copy(s, s, q);
+    wait_vm<2 * NC>();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int q = 0; q < NR; ++q) frag(sm + kg * SG, 0, q);
+#pragma unroll
+    for (int i = 0; i < TM - 2; ++i) frag_a(sm + kg * SG, 0, i);
+    int s0 = 0;                                          // stage kt lives in LDS stage kt % 3
+    for (int kt = 0; kt + 1 < nk; kt += 2) {
+        const int s1 = s0 == 2 ? 0 : s0 + 1, s2 = s1 == 2 ? 0 : s1 + 1;
+        step(kt, 0, s0, s1);
+        step(kt + 1, 1, s1, s2);
+        s0 = s2;
     }
+    if (nk % 2) step(nk - 1, 0, s0, s0 == 2 ? 0 : s0 + 1);
+    wait_vm<0>();                                        // no copy outlives the loop
     auto owns = [&](int i, int j) { return KG == 1 || (i * TN + j) % KG == kg; };
     if constexpr (KG > 1) {
         // every wave is past its last fragment read: the stages take the partial
@@ -229,25 +268,29 @@ hipError_t launch_mfma(const uint16_t* X, const uint8_t* state, const uint16_t* 
 
 }  // namespace
 
-// Every tile fills a CU's LDS, so a launch runs in rounds of 256 workgroups.  Up to
-// 128 x 128, the smallest tile that needs one round (rows of one launch: 64 x
-// 4096 50.8 -> 20.0 us on 32 x 32 tiles in eight k groups, 128 x 4096 49.2 ->
-// 29.8 on 32 x 64, 256 x 4096 49.4 -> 42.5 on 64 x 64, 512 x 4096 70.6 -> 49.7 on
-// 128 x 64, 1024 x 4096 81.4 -> 74.4 on 128 x 128, against 64 x 64 or 128 x 128
-// without k groups); up to 64 rows 32 x 32 whatever the grid (reading Ps bounds
-// it: 16 x 18944 272 us, 321 on 32 x 64).  Past one round, 256 x 128 (eight waves
-// of 64 x 64) takes 0.87 of the time of two 128 x 128 tiles: 4096 x 12288 2670 ->
-// 2149 us in 6 rounds, but 1024 x 12288 656 us in 2 against 629 in 3 of 128 x 128.
+// Every tile fills most of a CU's LDS, so a launch runs in rounds of 256 workgroups.
+// Up to 128 x 128, the smallest tile that needs one round (waves of 64 x 64 where the
+// tile holds them: 250 x 4096 25.4 us on 64 x 64 tiles of one such wave in four k
+// groups, 29.9 with four waves of 32 x 32; 512 x 4096 37.9 on 128 x 64, 40.9 with
+// waves of 64 x 32): 64 x 4096 15.0 us on 32 x 32 against 19.0 on 32 x 64, 128 x 4096
+// 19.6 on 32 x 64 against 23.5 on 64 x 64, 64 x 12288 135 on 64 x 64 against 148 on
+// 128 x 64, 128 x 12288 166 on 128 x 64 against 214 on 128 x 128.  Up to 32 rows 32 x
+// 32 whatever the grid (reading Ps bounds it, and a taller tile is padding: 16 x 4096
+// 14.4, 20.1 on 64 x 64; 32 x 18944 283, 322); at 64 rows its second round reads X
+// and fills half the chip again (64 x 12288 163, 64 x 18944 384 against 298 on 128 x
+// 128).  Past one round, 256 x 128 (eight waves of 64 x 64) takes about 0.87 of the
+// time of two 128 x 128 tiles: 4096 x 12288 1996 us in 6 rounds against 2094 in 12,
+// but 1024 x 12288 633 in 2 against 569 in 3.
 hipError_t launch_transform_fast(const uint16_t* X, const uint8_t* state, const uint16_t* Ps, int M, int K, int dm,
                                  int du, float* Xp, hipStream_t st) {
     auto rounds = [&](int bm, int bn) {
         return ((size_t)((M + bm - 1) / bm) * (size_t)((K + bn - 1) / bn) + 255) / 256;
     };
-    if (M <= 64 || rounds(32, 32) == 1)
+    if (M <= 32 || rounds(32, 32) == 1)
         return launch_mfma<1, 1, 2, 2, 8>(X, state, Ps, M, K, dm, du, Xp, st);
     if (rounds(32, 64) == 1) return launch_mfma<1, 2, 2, 2, 4>(X, state, Ps, M, K, dm, du, Xp, st);
-    if (rounds(64, 64) == 1) return launch_mfma<2, 2, 2, 2, 4>(X, state, Ps, M, K, dm, du, Xp, st);
-    if (rounds(128, 64) == 1) return launch_mfma<2, 2, 4, 2, 2>(X, state, Ps, M, K, dm, du, Xp, st);
+    if (rounds(64, 64) == 1) return launch_mfma<1, 1, 4, 4, 4>(X, state, Ps, M, K, dm, du, Xp, st);
+    if (rounds(128, 64) == 1) return launch_mfma<2, 1, 4, 4, 2>(X, state, Ps, M, K, dm, du, Xp, st);
     if (rounds(128, 128) == 1 || 100 * rounds(128, 128) < 174 * rounds(256, 128))
         return launch_mfma<1, 2, 8, 4, 2>(X, state, Ps, M, K, dm, du, Xp, st);
     return launch_mfma<4, 2, 4, 4, 1>(X, state, Ps, M, K, dm, du, Xp, st);
