@@ -14,19 +14,21 @@
 // within that bound of a rounding boundary; the fixed-order path is the one the
 // codes are defined by, this one trades that for the matrix cores.
 //
-// The kernel is the GEMM's three-stage direct-to-LDS pipeline on fp16
+// The kernel is the GEMM's direct-to-LDS pipeline on fp16
 // operands.  A stage holds one k step of 32 of x and the matching steps of both
 // halves of Ps (hi and lo) for each k group, so x is fetched and read from LDS
 // once for both: two v_mfma_f32_16x16x32_f16 per 16 x 16 tile and step (hi then
 // lo, into one accumulator), the gate applied in the epilogue, fp32 out.
-// What bounds it: at a thousand rows and more the fp16 matrix cores (busy 57 % of
-// the cycles at 4096 x 12288, where the card holds 1.95 GHz; 1.24 PFLOP/s executed)
-// and the LDS reads that feed them (a 64 x 64 wave reads 12 KB per 32 MFMAs, a 128 x
-// 64 one 16 KB per 64); below, the latency of the k steps a wave takes one after
-// another, which the k groups divide.  With a step's fragment reads and copies
-// issued ahead of its MFMAs the two took turns, as one or two waves per SIMD do not
-// cover for each other: 1024 x 12288 629 -> 569 us with them spread between the
-// MFMAs, 1024 x 4096 78 -> 64, 4096 x 12288 2155 -> 1996.
+// What bounds it: at a thousand rows and more the fp16 matrix cores (4096 x 12288:
+// 1.35 PFLOP/s executed, what a large bf16 product reaches on the card, whose clock
+// falls to 1.95 GHz under this load) and the LDS reads that feed them (a 64 x 64
+// wave reads 12 KB per 32 MFMAs, a 64 x 96 one 16 KB per 48, a 128 x 64 one 16 KB per
+// 64); below, the latency of the k steps a wave takes one after another, which the
+// k groups divide.  With a step's fragment reads and copies issued ahead of its MFMAs
+// the two took turns, as one or two waves per SIMD do not cover for each other: 1024
+// x 12288 629 -> 569 us with them spread between the MFMAs, 1024 x 4096 78 -> 64, 4096
+// x 12288 2155 -> 1996.  Reading both halves of a cache line together where one step
+// takes half of it: 4096 x 12288 1954 -> 1863, 16384 x 3584 711 -> 684.
 #include "tile_common.hpp"
 
 namespace sq {
@@ -59,16 +61,20 @@ __global__ __launch_bounds__(256) void split_basis_kernel(const float* __restric
 // KG > 1: KG sets of WM x WN waves share the tile and take turns over its k
 // steps; their sums meet in LDS.
 template <int WM, int WN, int TM, int TN, int KG>
-__global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_eu(2))) void transform_mfma_kernel(const uint16_t* __restrict__ X,
-                                                                     const uint8_t* __restrict__ state,
-                                                                     const uint16_t* __restrict__ Ps, int M, int K,
-                                                                     int dm, int du, float* __restrict__ Xp) {
+__global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_eu(2))) void transform_mfma_kernel(
+    const uint16_t* __restrict__ X, const uint8_t* __restrict__ state, const uint16_t* __restrict__ Ps, int M, int K,
+    int dm, int du, float* __restrict__ Xp) {
     constexpr int NW = WM * WN;
     constexpr int BM = 16 * WM * TM, BN = 16 * WN * TN;
     constexpr int AB = BM * kKStep, BB = BN * kKStep;   // bytes of one stage: x, then Ps hi, then Ps lo
     constexpr int SG = AB + 2 * BB, SB = KG * SG;
-    constexpr int LA = AB / 1024 / NW, LB = BB / 1024 / NW;
-    static_assert(LA * NW * 1024 == AB && LB * NW * 1024 == BB, "stage loads must divide evenly");
+    // 1 KB copies of one stage: x, then Ps hi, then Ps lo; copy q of a wave is number NW q + wave
+    constexpr int CA = AB / 1024, CB = BB / 1024, CN = CA + 2 * CB, NC = CN / NW;
+    static_assert(NC * NW == CN && CA % NW == 0, "stage copies must divide evenly, x and Ps apart");
+    // A step takes 64 bytes of a row, half a cache line.  With k groups the two halves
+    // are requested together; without, the copies of two steps go out together.
+    constexpr bool PAIR = KG == 1;
+    constexpr int NS = PAIR ? 4 : 3;                     // LDS stages
     extern __shared__ __attribute__((aligned(16))) uint8_t sm[];
 
     const int tid = threadIdx.x;
@@ -87,11 +93,11 @@ __global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_
     const u32x4 rB = sgpr_rsrc(Ps, (uint32_t)K * ldb);
     auto swz = [](int r) { return (r >> 1) & 3; };
 
-    // this lane's segment of the wave's first rows; later copies are 16 rows on each.
-    // Rows past M (columns past K) lie past the descriptor's end and read as zeros.
+    // this lane's segment of the tile's first rows; a copy takes 16 rows.  Rows past M
+    // (columns past K) lie past the descriptor's end and read as zeros.
     const uint32_t seg = 16 * ((lane % 4) ^ swz(lane / 4));
-    const uint32_t oa = (uint32_t)(row0 + 16 * wave * LA + lane / 4) * lda + seg;
-    const uint32_t ob = (uint32_t)(col0 + 16 * wave * LB + lane / 4) * ldb + seg;
+    const uint32_t oa = (uint32_t)(row0 + lane / 4) * lda + seg;
+    const uint32_t ob = (uint32_t)(col0 + lane / 4) * ldb + seg;
     // wave-uniform, kept apart from the vector part of an address: combined, every
     // copy's address takes a register of its own through the loop
     auto scalar = [](uint32_t o) {
@@ -104,18 +110,17 @@ __global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_
     auto copy = [&](int skt, int stage, int q) {
         const int kt = KG * skt + kg;                    // this k group's step
         const bool past = kt >= nk_all;
-        const uint8_t* d = sm + stage * SB + kg * SG;
-        const uint32_t ko = (uint32_t)kt * kKStep;
-        if (q < LA) {
+        const int c = q * NW + wave;
+        const uint32_t lds = lds_addr(sm + stage * SB + kg * SG + c * 1024), ko = (uint32_t)kt * kKStep;
+        if (q * NW < CA) {
             u32x4 r = rA;
             r[2] = past ? 0u : r[2];
-            dma16(r, lds_addr(d + (wave * LA + q) * 1024), oa + scalar(16 * q * lda + ko));
+            dma16(r, lds, oa + scalar(16 * c * lda + ko));
         } else {
-            const int u = (q - LA) / 2, lo = (q - LA) % 2;
+            const int j = c - CA, lo = j >= CB;
             u32x4 r = rB;
             r[2] = past ? 0u : r[2];
-            dma16(r, lds_addr(d + AB + lo * BB + (wave * LB + u) * 1024), 
-                  ob + scalar(16 * u * ldb + ko + (lo ? lo_off : 0)));
+            dma16(r, lds, ob + scalar(16 * (j - (lo ? CB : 0)) * ldb + (lo ? lo_off : 0) + ko));
         }
     };
 
@@ -146,12 +151,20 @@ __global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_
         else
             frag_a(st, set, TM - 1 - (q - 2 * TN));
     };
-    constexpr int NR = 2 * TN + (TM < 2 ? TM : 2), NC = LA + 2 * LB, NX = NR + NC, NM = 2 * TM * TN;
-    // multiplies stage kt (register set `set`, LDS stage s0, which the copies of
-    // stage kt + 3 then reuse) while the fragments of stage kt + 1 come in from s1
+    constexpr int NR = 2 * TN + (TM < 2 ? TM : 2), NM = 2 * TM * TN;
+    // multiplies stage kt (register set kt % 2, LDS stage s0) while the fragments of
+    // stage kt + 1 come in from s1.  The copies of stage kt + NS follow into s0; in
+    // pairs, an odd step issues those of kt + 3 and kt + 4 into the two free stages.
     auto step = [&](int kt, int set, int s0, int s1) {
+        constexpr int NX = NR + NC, N2 = 2 * NC;
         asm volatile("" ::: "memory");
-        wait_vm<NC>();                                   // stage kt + 1 has landed; this wave's reads of kt are done
+        // stage kt + 1 has landed; this wave's reads of kt are done
+        if (!PAIR)
+            wait_vm<(NS - 2) * NC>();
+        else if (set == 0)
+            wait_vm<2 * NC>();
+        else
+            wait_vm<0>();
         __builtin_amdgcn_s_barrier();                    // ... and every wave's
         asm volatile("" ::: "memory");
         const uint8_t* st = sm + s1 * SB + kg * SG;
@@ -167,37 +180,43 @@ __global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_
             for (int q = m * NX / NM; q < (m + 1) * NX / NM; ++q) {
                 if (q < NR)
                     frag(st, set ^ 1, q);
-                else
-                    copy(kt + 3, s0, q - NR);
+                else if (!PAIR)
+                    copy(kt + NS, s0, q - NR);
+            }
+            if (PAIR && set == 1) {
+#pragma unroll
+                for (int q = m * N2 / NM; q < (m + 1) * N2 / NM; ++q)
+                    copy(kt + 3 + q % 2, (kt + 3 + q % 2) % NS, q / 2);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
     };
 #pragma unroll
-    for (int s = 0; s < 3; ++s)
+    for (int s = 0; s < NS; ++s)
 #pragma unroll
         for (int q = 0; q < NC; ++q) copy(s, s, q);
-    wait_vm<2 * NC>();
+    wait_vm<(NS - 1) * NC>();
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
 #pragma unroll
     for (int q = 0; q < NR; ++q) frag(sm + kg * SG, 0, q);
 #pragma unroll
     for (int i = 0; i < TM - 2; ++i) frag_a(sm + kg * SG, 0, i);
-    int s0 = 0;                                          // stage kt lives in LDS stage kt % 3
+    auto next = [](int s) { return s == NS - 1 ? 0 : s + 1; };
+    int s0 = 0;                                          // stage kt lives in LDS stage kt % NS
     for (int kt = 0; kt + 1 < nk; kt += 2) {
-        const int s1 = s0 == 2 ? 0 : s0 + 1, s2 = s1 == 2 ? 0 : s1 + 1;
+        const int s1 = next(s0), s2 = next(s1);
         step(kt, 0, s0, s1);
         step(kt + 1, 1, s1, s2);
         s0 = s2;
     }
-    if (nk % 2) step(nk - 1, 0, s0, s0 == 2 ? 0 : s0 + 1);
+    if (nk % 2) step(nk - 1, 0, s0, next(s0));
     wait_vm<0>();                                        // no copy outlives the loop
     auto owns = [&](int i, int j) { return KG == 1 || (i * TN + j) % KG == kg; };
     if constexpr (KG > 1) {
         // every wave is past its last fragment read: the stages take the partial
         // sums, and each group adds up and stores the blocks it owns
-        static_assert((KG - 1) * NW * TM * TN * kWave * 16 <= 3 * SB, "k-group partial sums fit in the stages");
+        static_assert((KG - 1) * NW * TM * TN * kWave * 16 <= NS * SB, "k-group partial sums fit in the stages");
         __syncthreads();
         v4f* red = reinterpret_cast<v4f*>(sm);           // [KG - 1: the groups but the owner][NW][TM][TN][lane]
         auto slot = [&](int g, int i, int j) {
@@ -253,8 +272,8 @@ namespace {
 template <int WM, int WN, int TM, int TN, int KG>
 hipError_t launch_mfma(const uint16_t* X, const uint8_t* state, const uint16_t* Ps, int M, int K, int dm, int du,
                        float* Xp, hipStream_t st) {
-    constexpr int BM = 16 * WM * TM, BN = 16 * WN * TN, LDS = 3 * KG * (BM + 2 * BN) * kKStep;
-    static_assert(LDS <= 160 * 1024, "three stages fit in LDS");
+    constexpr int BM = 16 * WM * TM, BN = 16 * WN * TN, LDS = (KG == 1 ? 4 : 3) * KG * (BM + 2 * BN) * kKStep;
+    static_assert(LDS <= 160 * 1024, "the stages fit in LDS");
     const size_t tiles = (size_t)((M + BM - 1) / BM) * (size_t)((K + BN - 1) / BN);
     if (tiles > 0x7fffffffu) return hipErrorInvalidConfiguration;
     static std::atomic<int> lds_set[kMaxDevices];
@@ -278,9 +297,11 @@ hipError_t launch_mfma(const uint16_t* X, const uint8_t* state, const uint16_t* 
 // 32 whatever the grid (reading Ps bounds it, and a taller tile is padding: 16 x 4096
 // 14.4, 20.1 on 64 x 64; 32 x 18944 283, 322); at 64 rows its second round reads X
 // and fills half the chip again (64 x 12288 163, 64 x 18944 384 against 298 on 128 x
-// 128).  Past one round, 256 x 128 (eight waves of 64 x 64) takes about 0.87 of the
-// time of two 128 x 128 tiles: 4096 x 12288 1996 us in 6 rounds against 2094 in 12,
-// but 1024 x 12288 633 in 2 against 569 in 3.
+// 128).
+// Past one round, the least of rounds x time of a round, in the ratio 57 : 100 : 140
+// of 128 x 128, 256 x 128 (eight waves of 64 x 64) and 256 x 192 (64 x 96): 1024 x
+// 12288 570 us in 3 rounds, 650 in 2, 505 in 1; 4096 x 12288 2076 in 12, 1939 in 6,
+// 1832 in 4; 4096 x 4096 254 in 4, 209 in 2, 270 in 2; 16384 x 3584 790, 684, 667.
 hipError_t launch_transform_fast(const uint16_t* X, const uint8_t* state, const uint16_t* Ps, int M, int K, int dm,
                                  int du, float* Xp, hipStream_t st) {
     auto rounds = [&](int bm, int bn) {
@@ -291,9 +312,11 @@ hipError_t launch_transform_fast(const uint16_t* X, const uint8_t* state, const 
     if (rounds(32, 64) == 1) return launch_mfma<1, 2, 2, 2, 4>(X, state, Ps, M, K, dm, du, Xp, st);
     if (rounds(64, 64) == 1) return launch_mfma<1, 1, 4, 4, 4>(X, state, Ps, M, K, dm, du, Xp, st);
     if (rounds(128, 64) == 1) return launch_mfma<2, 1, 4, 4, 2>(X, state, Ps, M, K, dm, du, Xp, st);
-    if (rounds(128, 128) == 1 || 100 * rounds(128, 128) < 174 * rounds(256, 128))
-        return launch_mfma<1, 2, 8, 4, 2>(X, state, Ps, M, K, dm, du, Xp, st);
-    return launch_mfma<4, 2, 4, 4, 1>(X, state, Ps, M, K, dm, du, Xp, st);
+    if (rounds(128, 128) == 1) return launch_mfma<1, 2, 8, 4, 2>(X, state, Ps, M, K, dm, du, Xp, st);
+    const size_t t0 = 57 * rounds(128, 128), t1 = 100 * rounds(256, 128), t2 = 140 * rounds(256, 192);
+    if (t0 <= t1 && t0 <= t2) return launch_mfma<1, 2, 8, 4, 2>(X, state, Ps, M, K, dm, du, Xp, st);
+    if (t1 < t2) return launch_mfma<4, 2, 4, 4, 1>(X, state, Ps, M, K, dm, du, Xp, st);
+    return launch_mfma<4, 2, 4, 6, 1>(X, state, Ps, M, K, dm, du, Xp, st);
 }
 
 }  // namespace sq
