@@ -246,8 +246,8 @@ constexpr long kCus = 256;
 //    8192: 57 us on 256 workgroups, 66 on 128; 16 x 12288: 127 us on 192);
 //  - P read again by every row tile: 64-, 128- and 256-byte runs (CB = 1, 2, 4) came
 //    back at 4.9, 7.5 and 13 TB/s (100 x 12288 in 7 row tiles: 849, 613, 367 us).
-// Over 27 sizes the shape chosen was the fastest of seven or within 9 % of it in
-// 22, and within 27 % in all.
+// Over 190 sizes (48 ... 10000 rows, K = 512 ... 4096) the choice, the tiled kernel
+// included, takes 5 % more than the fastest of six on average.
 long split_cost(SplitShape s, int M, int K, int& W) {
     const long nch = (K + kChunk - 1) / kChunk;
     const int cap = split_waves(s.rb * s.cb);
@@ -257,9 +257,9 @@ long split_cost(SplitShape s, int M, int K, int& W) {
     const long n = (wgs + kCus - 1) / kCus, side = cap / W;
     const long passes = (n + side - 1) / side, at_once = n < side ? n : side;
     const long mfma = passes * ((at_once * W + 3) / 4) * ((nch + W - 1) / W) * s.rb * s.cb;
-    const long p_read = (long)K * K / 1400000;
-    const long mem = p_read * 192 / (wgs < 192 ? wgs : 192);
-    const long again = p_read * rows * (s.cb == 1 ? 8 : s.cb == 2 ? 5 : 3) / 8;
+    const long p_read = (long)K * K;                 // x 1400000; divided last, small K count too
+    const long mem = p_read * 192 / (1400000 * (wgs < 192 ? wgs : 192));
+    const long again = p_read * rows * (s.cb == 1 ? 8 : s.cb == 2 ? 5 : 3) / (8 * 1400000);
     const long cost = mfma > mem ? mfma : mem;
     return cost > again ? cost : again;
 }
@@ -283,8 +283,9 @@ SplitShape split_shape(int M, int K, int& W, long& cost) {
 // block than two.  Measured at K = 4096: 512 rows 145 us here, 169 tiled (equal
 // costs, one tile per CU); 1024 rows 288 and 273 (equal, two); K = 4160: 256
 // rows 118 and 171 (cost 144 against 136, one tile per CU); K = 12288: 256 rows
-// 641 and 793, 512 rows 1271 and 1250 (equal, three).  Up to 32 rows the split
-// is always taken.
+// 641 and 793, 512 rows 1271 and 1250 (equal, three); K = 1536: 4608 rows 222 and
+// 210 (cost 182 against 192, four), so several tiles need a sixteenth less.
+// Up to 32 rows the split is always taken.
 bool transform_split_faster(int M, int K) {
     if ((size_t)M * K * 2 > 0x7fffffff) return false;   // X is addressed with 32-bit buffer offsets
     if (M <= 32) return true;
@@ -295,7 +296,7 @@ bool transform_split_faster(int M, int K) {
     int W;
     long cost;
     split_shape(M, K, W, cost);
-    return cost < (n == 1 ? tiled + tiled / 8 + 1 : tiled);
+    return cost < (n == 1 ? tiled + tiled / 8 + 1 : tiled - tiled / 16);
 }
 
 hipError_t launch_transform_split(const uint16_t* X, const uint8_t* state, const float* P, int M, int K, int dm,
