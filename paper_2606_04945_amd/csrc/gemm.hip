@@ -23,7 +23,8 @@
 // through the buffer descriptors' range check.  Few tiles (M of 17 to a few
 // hundred) split K across workgroups; the int32 partial sums are then added
 // exactly by a small kernel.
-// M <= 48 has kernels of their own that stream the weights into registers.
+// Few rows (M <= 16, some shapes up to 48) have kernels of their own that stream
+// the weights into registers.
 //
 // BITS = 8 is the W8A8 variant (App. D): codes are int8 already, so the same
 // tiles feed the MFMA straight from LDS with no unpacking and no scaling.
@@ -347,10 +348,8 @@ __device__ __forceinline__ void skinny_store(const v4i& acc, int row0, int lg, i
     }
 }
 
-// Short-M kernels cover M <= 16 TM tokens with TM row tiles of 16, TM <= 3: at
-// four row tiles the activation unpacking outweighs what the kernels save over
-// the tiled one.
-constexpr int kShortMaxTiles = 3;
+// Short-M kernels cover M <= 16 TM tokens with TM row tiles of 16, TM <= 3 (see
+// stream_weights for where the tiled kernel takes over).
 
 // KW waves share one group of 16 columns and take turns over k, batch by batch
 // (wave w multiplies batches w, w + KW, ...); their partial sums meet in LDS.
@@ -938,10 +937,38 @@ Plan choose_k_groups(int M, int N, int K, int bits) {
     return none;
 }
 
+// Up to 48 rows: the kernels that stream the weights into registers, or the tiles in
+// k groups, whose workgroup reads a weight once for all its rows.  The streaming
+// kernels' time grows with the row tiles (each expands and multiplies on its own
+// wave), the tiles' hardly does (graph-replayed with rotating weights, 24 layers, 1
+// ... 50 rows; streaming -> k groups on fragment-ordered weights):
+//  - 33 to 48 rows: 48 x 4096 x 12288 14.8 -> 9.4 us, 48 x 3584 x 18944 20.2 -> 12.2,
+//    8-bit 48 x 12288 x 4096 28.1 -> 12.0, 48 x 24576 x 4096 41.9 -> 19.4; wide 4-bit
+//    layers from 40 rows (24576 x 4096: 33 rows 14.7 and 15.0, 48 15.6 and 15.0), wide
+//    8-bit ones from 32 k steps (16640 x 1024 at 48 rows 7.9 and 7.8);
+//  - 17 to 32: 32 x 4096 x 12288 11.5 -> 9.7, 32 x 4608 x 3584 7.6 -> 6.2, 8-bit 32 x
+//    512 x 4096 8.1 -> 5.8; narrow 4-bit layers from 24 rows (17 x 3584 x 3584 5.5 and
+//    5.9, 24 5.9 and 6.0), row-major ones from 16 k steps (1024 x 1024: 4.1 and 4.6);
+//  - up to 16: mid-width layers alone (16 x 6144 x 4096 6.5 -> 6.1, 8-bit 16 x 4608 x
+//    3584 8.5 -> 6.5; 16 x 12288 x 4096 7.8 and 8.2, 16 x 4096 x 4096 5.1 and 5.9).
+// Where the k groups stand back K would be split across workgroups, whose scratch
+// callers of so few rows do not provide.
+constexpr int kFewRows = 48;
+bool stream_weights(int M, int N, int K, int bits, bool frag) {
+    if (M > kFewRows) return false;
+    const int nk = (K * bits / 8 + kKB - 1) / kKB, groups = (N + 15) / 16;
+    const int cfg = choose_k_groups(M, N, K, bits).cfg;
+    if (M > 32) return N > 16384 ? (bits == 8 ? frag && nk < 32 : M < 40) : cfg < 0;
+    if (cfg != 10 && cfg != 11) return true;          // 64-row tiles would be half padding
+    if (!frag && nk < 16) return true;
+    if (M > 16) return bits == 4 && groups <= 256 && M < 24;
+    return groups <= 256 || groups > (bits == 8 ? 768 : 512) || (bits == 4 && M < 8);
+}
+
 // The production plan (from measured sweeps on MI355X, graph-replayed with
 // rotating weights):
-//  - M <= 48: the short-M kernels (weight streaming; activations shared in LDS
-//    for wide 4-bit layers, K split inside the workgroup otherwise);
+//  - M <= 48 where stream_weights says so: the short-M kernels (activations shared
+//    in LDS for wide 4-bit layers, K split inside the workgroup otherwise);
 //  - 4-bit codes with at least 448 tiles of 256 x 128 or of 128 x 128:
 //    256 x 128 (eight waves of 64 x 64) at 448 ... 512 tiles of it, else
 //    128 x 128 (four waves of 64 x 64) (see below);
@@ -960,10 +987,11 @@ Plan choose_k_groups(int M, int N, int K, int bits) {
 //  - otherwise 64 x 64 (four waves of 32 x 32); with few tiles (only where the
 //    k groups stand back, see choose_k_groups) split over K across workgroups,
 //    twice as deep for K >= 8192 and kept at 8 k steps or more per split.
-Plan choose_plan(int M, int N, int K, int bits, bool k_groups = true) {
+Plan choose_plan(int M, int N, int K, int bits, bool k_groups = true, bool frag = false) {
+    const bool few = k_groups ? stream_weights(M, N, K, bits, frag) : M <= kFewRows;
     const int nk = (K * bits / 8 + kKB - 1) / kKB;
     auto tiles = [&](int bm, int bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
-    if (M > 16 * kShortMaxTiles && k_groups) {
+    if (!few && k_groups) {
         const Plan p = choose_k_groups(M, N, K, bits);
         if (p.cfg >= 0) return p;
     }
@@ -975,7 +1003,7 @@ Plan choose_plan(int M, int N, int K, int bits, bool k_groups = true) {
         return s < 32 ? s : 32;
     };
     Plan p;
-    if (M <= 16 * kShortMaxTiles) {
+    if (few) {
         // one wave per 16 columns, all M <= 48 tokens in its MFMA row tiles.  Wide
         // 4-bit layers whose activation codes fit in LDS share them among
         // ceil(groups / 256) waves per workgroup (one workgroup per CU); the rest
@@ -1049,7 +1077,7 @@ Plan choose_plan(int M, int N, int K, int bits, bool k_groups = true) {
     return p;
 }
 
-// Fragment-ordered weights, M <= 48 (from graph-replayed sweeps with rotating
+// Fragment-ordered weights, few rows (from graph-replayed sweeps with rotating
 // weights): at most about one workgroup per CU.  Wide layers (>= 1024 column
 // groups): one wave per column group, activations in LDS; mid-width (>= 384):
 // two waves per column group, activations in LDS; 257-383 groups: two waves per
@@ -1112,9 +1140,9 @@ hipError_t launch_weights_to_frag(const uint8_t* Wq, int N, int K, uint8_t* Wf, 
 
 hipError_t launch_gemm_frag(const uint8_t* Aq, const float* s_a, const uint8_t* Wf, const float* s_w, int M, int N,
                             int K, uint16_t* Y, int32_t* acc, void* ws, hipStream_t st, int bits) {
-    if (M <= 16 * kShortMaxTiles)
+    if (stream_weights(M, N, K, bits, true))
         return launch_short_frag(choose_frag_short(M, N, K, bits), Aq, s_a, Wf, s_w, M, N, K, Y, acc, st, bits);
-    const Plan p = choose_plan(M, N, K, bits);   // the tiled plans of row-major weights
+    const Plan p = choose_plan(M, N, K, bits, true, true);   // the tiled plans of row-major weights
     int32_t* part = static_cast<int32_t*>(ws);
     hipError_t e;
     if (bits == 8) {
