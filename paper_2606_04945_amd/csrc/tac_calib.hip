@@ -262,19 +262,43 @@ __device__ __forceinline__ double rsqrt_full(double a) {
     return y * fma(-0.5 * a * y, y, 1.5);
 }
 
+// What a lane met in a sweep, and whether the sweep needs another one.  A sweep
+// rotates every pair to orthogonal once; what it leaves is what later rotations put
+// back: a rotation by t of columns p and q gives (r, p) up to t times what (r, q)
+// has.  So it is enough that no pair was farther than 2e-9 from orthogonal (far) and
+// no rotation larger than 5e-8 (turned): less than 1e-16 comes back each time.  That
+// is how columns of distinct norms end, whose rotations shrink with their products.
+// Columns of (nearly) equal norm, from repeated eigenvalues, turn by any angle on
+// rounding noise, so there every pair must be found orthogonal to working precision
+// (open: farther than 4e-15; rounding leaves at most about 1e-15 at G = 128).
+// Stopping at 2e-9 alone left them up to 4e-11 from LAPACK.
+struct Met {
+    bool far = false, open = false, turned = false;
+    __device__ __forceinline__ void publish(int* flags) const {
+        if (far) flags[0] = 1;
+        if (open) flags[1] = 1;
+        if (turned) flags[2] = 1;
+    }
+    __device__ __forceinline__ static bool again(const int* flags) { return flags[0] | (flags[1] & flags[2]); }
+};
+
 // The rotation (x, y) <- (c x - s y, s x + c y) that makes columns of squared
 // norms al, be and product ga orthogonal: t = sign(z) / (|z| + sqrt(1 + z^2)),
 // z = (be - al) / (2 ga), c = 1 / sqrt(1 + t^2), s = t c.  c and s must be
 // orthonormal to working precision; t only decides how much of ga the rotation
 // removes, so it is formed with the hardware's approximate reciprocal and
-// reciprocal square root (a relative 1e-7 of ga is left, which the next sweep
-// takes).
-__device__ __forceinline__ void rotation(double al, double be, double ga, double& c, double& s) {
+// reciprocal square root (a relative 1e-7 of ga is left).  `met` takes what the
+// pair says about the sweep.
+__device__ __forceinline__ void rotation(double al, double be, double ga, double& c, double& s, Met& met) {
     const double z = (be - al) * __builtin_amdgcn_rcp(2.0 * ga);
     const double h = fma(z, z, 1.0);
     double t = __builtin_amdgcn_rcp(fabs(z) + h * __builtin_amdgcn_rsq(h));
     t = fabs(z) < 1e100 ? copysign(t, z) : 0.5 * __builtin_amdgcn_rcp(z);   // z^2 would overflow
-    t = ga * ga > 1e-32 * al * be ? t : 0.0;              // orthogonal already (or a zero column)
+    const double g2 = ga * ga, ab = al * be;
+    t = g2 > 1e-32 * ab ? t : 0.0;                        // orthogonal already (or a zero column)
+    met.far |= g2 > 4e-18 * ab;
+    met.open |= g2 > 1.6e-29 * ab;
+    met.turned |= fabs(t) > 5e-8;
     c = rsqrt_full(fma(t, t, 1.0));
     s = t * c;
 }
@@ -289,17 +313,15 @@ __device__ __forceinline__ void rotation(double al, double be, double ga, double
 // a lane reads its rows of both columns, the three products meet over the lanes
 // by DPP, every lane forms the rotation itself and writes its rows back, so a
 // round is one LDS round trip and one barrier (none up to G = 16, where a wave
-// holds all pairs).  Sweeps end after one that met no pair of columns farther
-// than 2e-9 from orthogonal: convergence is quadratic, so the sweep itself took
-// those to working precision.
+// holds all pairs).  Sweeps end as Met says.
 // Bound by the latency of a round (0.4 us at G = 16: one wave per block and
 // little more than one chain of dependent fp64 instructions).  The two-sided
 // form for the eigendecompositions took three passes over LDS and three
 // barriers a round, with the rotations formed by a few threads by full-precision
 // divides and square roots: the closed form of 256 blocks of 16 took 417 us, now
-// 91; of 32 blocks of 128, 26 ms, now 4.2.
+// 97; of 32 blocks of 128, 26 ms, now 4.4.
 template <int G>
-__device__ __forceinline__ void jacobi_columns(double* W, double* V, int* flag) {
+__device__ __forceinline__ void jacobi_columns(double* W, double* V, int* flags) {
     using Sh = SolveShape<G>;
     constexpr int NT = Sh::NT, LPP = Sh::LPP, RPT = Sh::RPT, H = Sh::H;
     const int tid = threadIdx.x;
@@ -309,9 +331,9 @@ __device__ __forceinline__ void jacobi_columns(double* W, double* V, int* flag) 
     const int t = tid / LPP, j = tid % LPP;
     const bool on = t < H;                                // G < 16 leaves lanes of the wave idle
     for (int sweep = 0; sweep < 60; ++sweep) {
-        if (tid == 0) *flag = 0;
+        if (tid < 3) flags[tid] = 0;
         sync<NT>();
-        bool far = false;
+        Met met;
         int a = t, b = G - 1 - t;                         // players of positions t and G - 1 - t in round 0
         for (int r = 0; r < G - 1; ++r) {
             if (on) {
@@ -330,8 +352,7 @@ __device__ __forceinline__ void jacobi_columns(double* W, double* V, int* flag) 
                 }
                 al = lanes_sum<LPP>(al), be = lanes_sum<LPP>(be), ga = lanes_sum<LPP>(ga);
                 double c, s;
-                rotation(al, be, ga, c, s);
-                far |= ga * ga > 4e-18 * al * be;
+                rotation(al, be, ga, c, s, met);
 #pragma unroll
                 for (int k = 0; k < RPT; ++k) {
                     W[p * G + j + LPP * k] = fma(c, x[k], -s * y[k]);
@@ -345,9 +366,9 @@ __device__ __forceinline__ void jacobi_columns(double* W, double* V, int* flag) 
             b = b == G - 1 ? 1 : b + 1;
             sync<NT>();
         }
-        if (far) *flag = 1;
+        met.publish(flags);
         sync<NT>();
-        const bool again = *flag != 0;
+        const bool again = Met::again(flags);
         sync<NT>();
         if (!again) break;
     }
@@ -362,7 +383,7 @@ __device__ __forceinline__ void jacobi_columns(double* W, double* V, int* flag) 
 // again.  cs[t] holds a round's rotation of pair t, s signed so that it applies
 // to (position t, position G - 1 - t).
 template <int G>
-__device__ __forceinline__ void jacobi_columns_vreg(double* W, double* Vout, double2* cs, int* flag) {
+__device__ __forceinline__ void jacobi_columns_vreg(double* W, double* Vout, double2* cs, int* flags) {
     using Sh = SolveShape<G>;
     constexpr int LPP = Sh::LPP, RPT = Sh::RPT;
     static_assert(Sh::NT == 8 * G && G / 16 == 8, "eight lanes per row, eight pairs each");
@@ -377,9 +398,9 @@ __device__ __forceinline__ void jacobi_columns_vreg(double* W, double* Vout, dou
     }
     __syncthreads();
     for (int sweep = 0; sweep < 60; ++sweep) {
-        if (tid == 0) *flag = 0;
+        if (tid < 3) flags[tid] = 0;
         __syncthreads();
-        bool far = false;
+        Met met;
         int a = t, b = G - 1 - t;
         for (int r = 0; r < G - 1; ++r) {
             const int p = a < b ? a : b, q = a < b ? b : a;
@@ -395,8 +416,7 @@ __device__ __forceinline__ void jacobi_columns_vreg(double* W, double* Vout, dou
             }
             al = lanes_sum<LPP>(al), be = lanes_sum<LPP>(be), ga = lanes_sum<LPP>(ga);
             double c, s;
-            rotation(al, be, ga, c, s);
-            far |= ga * ga > 4e-18 * al * be;
+            rotation(al, be, ga, c, s, met);
             double2* out = cs + (r & 1) * (G / 2);        // two rounds' worth: the last round's readers may lag
             if (j == 0) out[t % 8 * 8 + t / 8] = make_double2(c, a == p ? s : -s);
 #pragma unroll
@@ -427,9 +447,9 @@ __device__ __forceinline__ void jacobi_columns_vreg(double* W, double* Vout, dou
             for (int i = 7; i > 0; --i) hi[i] = hi[i - 1];
             hi[0] = vj == 0 ? first : from_prev;
         }
-        if (far) *flag = 1;
+        met.publish(flags);
         __syncthreads();
-        const bool again = *flag != 0;
+        const bool again = Met::again(flags);
         __syncthreads();
         if (!again) break;
     }
@@ -499,7 +519,7 @@ __global__ __launch_bounds__(SolveShape<G>::NT) void tac_power_kernel(const doub
     extern __shared__ __attribute__((aligned(16))) double mats[];
     __shared__ double mu[G], w[G];
     __shared__ double2 cs[Sh::VREG ? G : 1];
-    __shared__ int flag;
+    __shared__ int flags[3];
     double* W = mats;
     const int tid = threadIdx.x, b = blockIdx.x, pass = blockIdx.y;
     const size_t stride = GG + G;
@@ -539,9 +559,9 @@ __global__ __launch_bounds__(SolveShape<G>::NT) void tac_power_kernel(const doub
         sync<NT>();
     }
     if constexpr (Sh::VREG)
-        jacobi_columns_vreg<G>(W, V, cs, &flag);
+        jacobi_columns_vreg<G>(W, V, cs, flags);
     else
-        jacobi_columns<G>(W, V, &flag);
+        jacobi_columns<G>(W, V, flags);
     column_sums<G, NT>([&](int j, int i) { return V[j * G + i] * W[j * G + i]; },
                        [&](int j, double l) {
                            l = fmax(l, kEigFloor);
@@ -570,7 +590,7 @@ __global__ __launch_bounds__(SolveShape<G>::NT) void tac_match_kernel(double* __
     extern __shared__ __attribute__((aligned(16))) double mats[];
     __shared__ double sig[G], w[G], muq[G];
     __shared__ double2 cs[Sh::VREG ? G : 1];
-    __shared__ int flag;
+    __shared__ int flags[3];
     double* W = mats;
     const int tid = threadIdx.x, b = blockIdx.x;
     double* base = block_scratch<G>(wk, b);
@@ -583,9 +603,9 @@ __global__ __launch_bounds__(SolveShape<G>::NT) void tac_match_kernel(double* __
                    [&](int i, int j, double s) { W[j * G + i] = s; });
     sync<NT>();
     if constexpr (Sh::VREG)
-        jacobi_columns_vreg<G>(W, V, cs, &flag);
+        jacobi_columns_vreg<G>(W, V, cs, flags);
     else
-        jacobi_columns<G>(W, V, &flag);
+        jacobi_columns<G>(W, V, flags);
     column_sums<G, NT>([&](int j, int i) { return W[j * G + i] * W[j * G + i]; },
                        [&](int j, double s) { sig[j] = sqrt(s); });
     sync<NT>();
