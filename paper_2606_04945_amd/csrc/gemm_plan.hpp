@@ -29,6 +29,7 @@ struct Plan {
                    // cfg 6: column groups per workgroup
     int kw;        // cfg 6: waves per column group, taking turns over k
     bool alds;     // cfg 6: activation fragments staged in LDS (else read from L2)
+    bool whole;    // cfg 6: ... with no fewer column groups per workgroup for it
     int u, d;      // cfg 6: k steps per batch, batches in the register ring
 };
 
@@ -39,7 +40,7 @@ Plan make_plan(int M, int N, int K, int bm, int bn, int want_splits, int bits = 
     p.cfg = -1;
     p.waves = 1;
     p.kw = 1;
-    p.alds = false;
+    p.alds = p.whole = false;
     p.u = 2;
     p.d = 4;
     p.bm = bm;
@@ -104,37 +105,108 @@ Plan choose_k_groups(int M, int N, int K, int bits) {
     return none;
 }
 
+// Fragment-ordered weights, few rows (from graph-replayed sweeps with rotating
+// weights): at most about one workgroup per CU.  Wide layers (>= 1024 column
+// groups): one wave per column group, activations in LDS; mid-width (>= 384):
+// two waves per column group, activations in LDS; 257-383 groups: two waves per
+// group, two groups per workgroup, activations in LDS (one group per workgroup
+// would leave some CUs twice the work of the rest); up to 256: four waves per
+// column group, one group per workgroup, activations from L2, a ring of two
+// batches from 17 tokens on.  Batches of two k steps, or of one where that
+// leaves fewer zero-weight k steps in the last pass of the ring.  At least two
+// batches per wave.
+Plan choose_frag_short(int M, int N, int K, int bits) {
+    const int nk = (K * bits / 8 + kKB - 1) / kKB, nb = (nk + 1) / 2;
+    const int groups = (N + 15) / 16, tm = (M + 15) / 16;
+    Plan p = make_plan(M, N, K, 16 * tm, 16, 1, bits);
+    p.cfg = 6;
+    int kw, cg;
+    bool alds;
+    if (groups >= 1024) {
+        kw = 1, cg = (groups + 255) / 256, alds = true;
+    } else if (groups >= 384) {
+        kw = 2, cg = tm == 1 ? (groups + 255) / 256 : (groups + 191) / 192, alds = true;
+    } else if (groups > 256) {
+        kw = 2, cg = 2, alds = true;
+    } else {
+        kw = 4, cg = 1, alds = false;
+    }
+    while (kw > 1 && nb < 2 * kw) kw /= 2;
+    const int cg0 = cg;
+    if (alds) {   // staged activations that do not fit in LDS are read from L2 instead
+        cg = cg < 16 / kw ? cg : 16 / kw;
+        p.whole = frag_lds_bytes(tm, nk, kw, cg, true) <= kFragMaxLds;
+        while (cg > 1 && frag_lds_bytes(tm, nk, kw, cg, true) > kFragMaxLds) --cg;
+        alds = frag_lds_bytes(tm, nk, kw, cg, true) <= kFragMaxLds;
+    }
+    if (!alds) cg = cg0 < 8 / kw ? cg0 : 8 / kw;
+    p.waves = cg;
+    p.kw = kw;
+    p.alds = alds;
+    p.d = !alds && kw == 4 && tm > 1 ? 2 : 4;
+    // k steps a wave multiplies past the end: its batches rounded up to whole passes of the ring
+    auto waste = [&](int u) {
+        const int batches = (nk + u - 1) / u, per_wave = (batches + kw - 1) / kw;
+        return (((per_wave + p.d - 1) / p.d) * p.d * kw - batches) * u;
+    };
+    p.u = alds && waste(1) < waste(2) ? 1 : 2;
+    return p;
+}
+
 // Up to 48 rows: the kernels that stream the weights into registers, or the tiles in
 // k groups, whose workgroup reads a weight once for all its rows.  The streaming
 // kernels' time grows with the row tiles (each expands and multiplies on its own
-// wave), the tiles' hardly does (graph-replayed with rotating weights, 24 layers, 1
-// ... 50 rows; streaming -> k groups on fragment-ordered weights):
-//  - 33 to 48 rows: 48 x 4096 x 12288 14.8 -> 9.4 us, 48 x 3584 x 18944 20.2 -> 12.2,
-//    8-bit 48 x 12288 x 4096 28.1 -> 12.0, 48 x 24576 x 4096 41.9 -> 19.4; wide 4-bit
-//    layers from 40 rows (24576 x 4096: 33 rows 14.7 and 15.0, 48 15.6 and 15.0), wide
-//    8-bit ones from 32 k steps (16640 x 1024 at 48 rows 7.9 and 7.8);
-//  - 17 to 32: 32 x 4096 x 12288 11.5 -> 9.7, 32 x 4608 x 3584 7.6 -> 6.2, 8-bit 32 x
-//    512 x 4096 8.1 -> 5.8; narrow 4-bit layers from 24 rows (17 x 3584 x 3584 5.5 and
-//    5.9, 24 5.9 and 6.0), row-major ones from 16 k steps (1024 x 1024: 4.1 and 4.6);
-//  - up to 16: mid-width layers alone (16 x 6144 x 4096 6.5 -> 6.1, 8-bit 16 x 4608 x
-//    3584 8.5 -> 6.5; 16 x 12288 x 4096 7.8 and 8.2, 16 x 4096 x 4096 5.1 and 5.9).
+// wave) and most where the activations no longer fit in LDS; the tiles keep fewer
+// weights in flight per wave, so they gain least on weights that come from HBM.
+// Streaming -> k groups, 7000 shapes of 1 ... 48 rows, graph-replayed over 340 MB of
+// weights in turn (with eight in turn the same but for row-major weights, which
+// come out 10-20 % better for the k groups from the caches):
+//  - up to 16 rows, fragment-ordered weights: always streamed (16 x 6144 x 4096 5.5 ->
+//    6.0 us, 8-bit 4-30 % slower: 12 x 4104 x 4096 6.6 -> 7.7).  Row-major ones:
+//    mid-width layers of more k steps (257 ... 512 column groups 0.8-0.95 of the time);
+//  - 17 to 32 rows, up to 256 groups: streamed (24 x 3584 x 6144 5.9 -> 7.2, 8-bit
+//    24 x 3072 x 4096 6.6 -> 8.5; row-major 28 x 2048 x 6144 11.2 -> 12.6);
+//  - 17 to 32, wider, fragment-ordered: k groups where the activations do not fit
+//    (8-bit 30 x 7168 x 9216 31.7 -> 19.3), and for 4-bit codes at 257 ... 512 groups
+//    (18 x 7168 x 3584 7.4 -> 6.0) and more k steps past 768 (20 x 16384 x 9216 18.6
+//    -> 16.5; 20 x 12288 x 4096 8.4 -> 8.5); row-major from 16 steps (20 x 8192 x
+//    4096 8.0 -> 6.8), wider 4-bit layers from 24;
+//  - 33 to 48 rows: k groups (40 x 4608 x 9216 16.9 -> 10.9, 8-bit 48 x 5120 x 12288
+//    39 -> 23), but for the shallowest K (up to 30 % slower), 8-bit codes past 512
+//    groups while the activations fit (up to 15 % slower), and numbers of steps that
+//    just fill passes of the streaming ring (13 ... 16; 25 ... 32 up to 36 rows: 33 x
+//    2616 x 3776 5.0 -> 5.4) up to 256 groups;
+//  - 33 to 48, past 1024 groups: while the activations fit, streamed (36 x 24576 x
+//    2560 8-bit 14.6 -> 16.4), then not (44 x 37888 x 12288 146 -> 55); 4-bit codes
+//    below 40 rows always.
 // Where the k groups stand back K would be split across workgroups, whose scratch
 // callers of so few rows do not provide.
 constexpr int kFewRows = 48;
 bool stream_weights(int M, int N, int K, int bits, bool frag) {
     if (M > kFewRows) return false;
-    const int nk = (K * bits / 8 + kKB - 1) / kKB, groups = (N + 15) / 16;
+    const int nk = (K * bits / 8 + kKB - 1) / kKB, groups = (N + 15) / 16, tm = (M + 15) / 16;
     const int cfg = choose_k_groups(M, N, K, bits).cfg;
-    if (M > 32) return N > 16384 ? (bits == 8 ? frag && nk < 32 : M < 40) : cfg < 0;
-    if (cfg != 10 && cfg != 11) return true;          // 64-row tiles would be half padding
-    if (!frag && nk < 16) return true;
-    if (M > 16) return bits == 4 && groups <= 256 && M < 24;
-    return groups <= 256 || groups > (bits == 8 ? 768 : 512) || (bits == 4 && M < 8);
+    const bool fits = frag ? choose_frag_short(M, N, K, bits).whole : shared_lds_bytes(tm, nk) > 0;
+    if (M > 32) {
+        if (groups > 1024) return bits == 8 ? (frag ? fits : nk <= 4) : fits || M < 40;
+        if (cfg < 0) return true;
+        if (!frag) return nk <= (bits == 8 && groups > 512 ? 6 : 8);
+        if (groups <= 256)
+            return (bits == 8 && nk <= 6) || (nk > 12 && nk <= 16) || (bits == 4 && M <= 36 && nk > 24 && nk <= 32);
+        return fits && (bits == 4 ? nk <= 8 : groups > 512 || nk <= 16);
+    }
+    if ((cfg != 10 && cfg != 11) || groups <= 256) return true;   // 64-row tiles would be half padding
+    if (M > 16) {
+        if (!frag) return nk < (bits == 4 && groups > 512 ? 24 : 16);
+        return fits && (bits == 8 || (groups <= 512 ? nk <= 8 : groups <= 768 || nk <= 24));
+    }
+    if (frag) return true;
+    return bits == 8 ? M <= 8 || nk < 30 || groups > 768 : M < 8 || nk <= 16 || groups > 512;
 }
 
 // The production plan (from measured sweeps on MI355X, graph-replayed with
 // rotating weights):
-//  - M <= 48 where stream_weights says so: the short-M kernels (activations shared
+//  - up to 48 rows where stream_weights says so: the short-M kernels (activations shared
 //    in LDS for wide 4-bit layers, K split inside the workgroup otherwise);
 //  - 4-bit codes with at least 448 tiles of 256 x 128 or of 128 x 128:
 //    256 x 128 (eight waves of 64 x 64) at 448 ... 512 tiles of it, else
@@ -241,53 +313,6 @@ Plan choose_plan(int M, int N, int K, int bits, bool k_groups = true, bool frag 
         p = make_plan(M, N, K, 64, 64, splits_for(tiles(64, 64)), bits);
         p.cfg = 2;
     }
-    return p;
-}
-
-// Fragment-ordered weights, few rows (from graph-replayed sweeps with rotating
-// weights): at most about one workgroup per CU.  Wide layers (>= 1024 column
-// groups): one wave per column group, activations in LDS; mid-width (>= 384):
-// two waves per column group, activations in LDS; 257-383 groups: two waves per
-// group, two groups per workgroup, activations in LDS (one group per workgroup
-// would leave some CUs twice the work of the rest); up to 256: four waves per
-// column group, one group per workgroup, activations from L2, a ring of two
-// batches from 17 tokens on.  Batches of two k steps, or of one where that
-// leaves fewer zero-weight k steps in the last pass of the ring.  At least two
-// batches per wave.
-Plan choose_frag_short(int M, int N, int K, int bits) {
-    const int nk = (K * bits / 8 + kKB - 1) / kKB, nb = (nk + 1) / 2;
-    const int groups = (N + 15) / 16, tm = (M + 15) / 16;
-    Plan p = make_plan(M, N, K, 16 * tm, 16, 1, bits);
-    p.cfg = 6;
-    int kw, cg;
-    bool alds;
-    if (groups >= 1024) {
-        kw = 1, cg = (groups + 255) / 256, alds = true;
-    } else if (groups >= 384) {
-        kw = 2, cg = tm == 1 ? (groups + 255) / 256 : (groups + 191) / 192, alds = true;
-    } else if (groups > 256) {
-        kw = 2, cg = 2, alds = true;
-    } else {
-        kw = 4, cg = 1, alds = false;
-    }
-    while (kw > 1 && nb < 2 * kw) kw /= 2;
-    const int cg0 = cg;
-    if (alds) {   // staged activations that do not fit in LDS are read from L2 instead
-        cg = cg < 16 / kw ? cg : 16 / kw;
-        while (cg > 1 && frag_lds_bytes(tm, nk, kw, cg, true) > kFragMaxLds) --cg;
-        alds = frag_lds_bytes(tm, nk, kw, cg, true) <= kFragMaxLds;
-    }
-    if (!alds) cg = cg0 < 8 / kw ? cg0 : 8 / kw;
-    p.waves = cg;
-    p.kw = kw;
-    p.alds = alds;
-    p.d = !alds && kw == 4 && tm > 1 ? 2 : 4;
-    // k steps a wave multiplies past the end: its batches rounded up to whole passes of the ring
-    auto waste = [&](int u) {
-        const int batches = (nk + u - 1) / u, per_wave = (batches + kw - 1) / kw;
-        return (((per_wave + p.d - 1) / p.d) * p.d * kw - batches) * u;
-    };
-    p.u = alds && waste(1) < waste(2) ? 1 : 2;
     return p;
 }
 

@@ -61,3 +61,17 @@ def test_gemm_scratch_fits_the_workspace(plans):
             p = gemm(plans, M, N, K, bits, frag)
             if p["splits"] > 1:
                 assert p["splits"] * M * N * 4 <= ws, (M, N, K, bits, frag)
+
+
+# Measured on weights that come from memory, us streamed and in k groups; the call takes
+# the faster one
+@pytest.mark.parametrize("M,N,K,bits,frag,streamed,tiled", [
+    (16, 6144, 4096, 4, True, 5.5, 6.0), (12, 4104, 4096, 8, True, 6.6, 7.7), (16, 9216, 4096, 8, True, 9.7, 11.2),
+    (24, 3584, 6144, 4, True, 5.9, 7.2), (24, 3072, 4096, 8, True, 6.6, 8.5), (28, 2048, 6144, 8, False, 11.2, 12.6),
+    (32, 12288, 5120, 4, True, 10.1, 10.4), (22, 10240, 3584, 8, True, 10.2, 10.6), (36, 24576, 2560, 8, True, 14.6, 16.4),
+    (8, 12288, 64, 8, True, 2.6, 4.1), (32, 512, 16384, 4, True, 11.3, 13.5),
+    (18, 7168, 3584, 4, True, 7.4, 6.0), (30, 7168, 9216, 8, True, 31.7, 19.3), (20, 8192, 4096, 4, False, 8.0, 6.8),
+    (16, 6144, 4096, 4, False, 6.5, 6.1), (40, 4608, 9216, 4, True, 16.9, 10.9), (48, 5120, 12288, 8, True, 39.2, 23.2),
+    (44, 37888, 12288, 4, True, 146.0, 55.0), (40, 20480, 3072, 8, False, 31.6, 23.3)])
+def test_few_rows_take_the_faster_kernel(plans, M, N, K, bits, frag, streamed, tiled):
+    assert (gemm(plans, M, N, K, bits, frag)["cfg"] in STREAM) == (streamed < tiled)
