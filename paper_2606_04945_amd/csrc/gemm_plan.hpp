@@ -70,8 +70,8 @@ size_t frag_lds_bytes(int tm, int nk, int kw, int cg, bool alds) {
 // are bound by the latency of the k steps, not by operands or MFMAs: the time
 // follows the number of steps a wave takes, so the smallest tile that still
 // fits one round wins, for 4-bit and 8-bit codes alike (65 shapes, 50 ... 2000
-// rows, N = 512 ... 37888, K = 1024 ... 32768, against every tile below and the
-// former plans).  4-bit, former plan -> k groups: 50 x 4096 x 4096 7.7 -> 5.2 us
+// rows, N = 512 ... 37888, K = 1024 ... 32768, eight weights in turn, against every
+// tile below and the former plans).  4-bit, former plan -> k groups: 50 x 4096 x 4096 7.7 -> 5.2 us
 // (32 x 32 tiles), 64 x 12288 x 4096 12.6 -> 9.7 (64 x 64), 128 x 4096 x 12288
 // 17.5 -> 14.0 (32 x 64), 250 x 4096 x 12288 25.9 -> 18.5 (64 x 64), 250 x 3584
 // x 18944 37.1 -> 25.7, 512 x 4096 x 12288 37.9 -> 29.1 (64 x 128); 8-bit: 250 x
@@ -204,6 +204,40 @@ bool stream_weights(int M, int N, int K, int bits, bool frag) {
     return bits == 8 ? M <= 8 || nk < 30 || groups > 768 : M < 8 || nk <= 16 || groups > 512;
 }
 
+// Above 48 rows: whether k groups (plan p) beat the plan without them.  A k group
+// takes w = nk / KG steps one after another, a workgroup of the K split `per` steps,
+// and the split's second launch costs about 4 us; 8000 shapes of 49 ... 2000 rows,
+// graph-replayed over 340 MB of weights in turn, other plan -> k groups:
+//  - a shallow K leaves most groups idle: 128 x 128 x 64 3.0 -> 3.8 us, 200 x 8192 x
+//    512 5.1 -> 6.1 (up to 64 rows of fragment-ordered 4-bit weights up to 12288 wide
+//    k groups are the faster ones there too);
+//  - a deep K on few tiles: the split has more workgroups than CUs to share it, 64 x
+//    64 x 65536 17 -> 29 us, 8-bit 250 x 64 x 65536 19 -> 61.  32 x 32 tiles hold up
+//    to 8 steps a group, to 13 where the split is not two steps shorter or the
+//    weights are read by several row tiles either way (64 x 2048 x 9216 8-bit 13.1 ->
+//    16.6, 100 x 1024 x 9216 15.2 -> 11.0), and to 16 against long splits; 32 x 64
+//    tiles to 16 steps (24 against six splits, 48 against four), 64 x 64 tiles
+//    to 40 against four, to 64 at 8 bits;
+//  - two groups are no faster than four waves of a 64 x 64 tile up to 16 steps at 8
+//    bits and 28 at 4 bits (up to 25 % slower below; 5-15 % faster past it).
+bool k_groups_faster(const Plan& p, const Plan& other, int M, int N, int nk, int bits, bool frag) {
+    const bool shallow = !(frag && bits == 4 && M <= 64 && N <= 12288);
+    const int w10 = (nk + 11) / 12, w11 = (nk + 7) / 8, w12 = (nk + 3) / 4;
+    switch (p.cfg) {
+        case 10:
+            if (shallow && nk <= (bits == 8 ? 6 : 3)) return false;
+            return w10 <= 8 || (w10 <= 13 && (M > 64 || other.per >= w10 - 1)) || (w10 <= 16 && other.per >= w10 - 2);
+        case 11:
+            if (shallow && nk <= 6) return false;
+            return w11 <= (other.splits <= 4 ? 48 : other.splits <= 6 ? 24 : 16);
+        case 12:
+            if (shallow && nk <= 7) return false;
+            return w12 <= (bits == 8 ? 64 : 40) || other.splits < 4;
+        case 13: return other.cfg != 2 || nk >= (bits == 8 ? 20 : 32);
+        default: return true;
+    }
+}
+
 // The production plan (from measured sweeps on MI355X, graph-replayed with
 // rotating weights):
 //  - up to 48 rows where stream_weights says so: the short-M kernels (activations shared
@@ -220,19 +254,20 @@ bool stream_weights(int M, int N, int K, int bits, bool frag) {
 //    of its tiles; else 128 x 128 (four waves) from 192 of its tiles;
 //  - at most 256 tiles of 32 x 32, 32 x 64, 64 x 64 or 64 x 128: the smallest
 //    of these, in k groups (choose_k_groups);
-//  - 129 ... 256 tiles of 128 x 128 and at least 128 k steps (48 for 8-bit
-//    codes): 128 x 128 with two k groups of four waves (see below);
+//  - 129 ... 256 tiles of 128 x 128 and at least 128 k steps (48 for 8-bit codes,
+//    49 up to 160 tiles): 128 x 128 with two k groups of four waves (see below);
 //  - at least 512 tiles of 64 x 128: 64 x 128 (four waves of 64 x 32);
 //  - otherwise 64 x 64 (four waves of 32 x 32); with few tiles (only where the
 //    k groups stand back, see choose_k_groups) split over K across workgroups,
 //    twice as deep for K >= 8192 and kept at 8 k steps or more per split.
-Plan choose_plan(int M, int N, int K, int bits, bool k_groups = true, bool frag = false) {
+Plan choose_plan(int M, int N, int K, int bits, bool k_groups, bool frag = false) {
     const bool few = k_groups ? stream_weights(M, N, K, bits, frag) : M <= kFewRows;
     const int nk = (K * bits / 8 + kKB - 1) / kKB;
     auto tiles = [&](int bm, int bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
     if (!few && k_groups) {
         const Plan p = choose_k_groups(M, N, K, bits);
-        if (p.cfg >= 0) return p;
+        if (p.cfg >= 0 && M <= kFewRows) return p;
+        if (p.cfg >= 0 && k_groups_faster(p, choose_plan(M, N, K, bits, false), M, N, nk, bits, frag)) return p;
     }
     auto splits_for = [&](int t) {
         int s = t >= 256 ? 1 : (256 + t - 1) / t;
@@ -261,7 +296,7 @@ Plan choose_plan(int M, int N, int K, int bits, bool k_groups = true, bool frag 
             p.cfg = 3;
             p.waves = kw;
         }
-    } else if (tiles(128, 128) > 128 && tiles(128, 128) <= 256 && nk >= (bits == 8 ? (k_groups ? 48 : 64) : 128)) {
+    } else if (tiles(128, 128) > 128 && tiles(128, 128) <= 256 && nk >= (bits == 8 ? (!k_groups ? 64 : tiles(128, 128) > 160 ? 48 : 49) : 128)) {
         // at most one 128 x 128 tile per CU and a deep K: two k groups of four
         // waves per tile (interleaved timings with rotating weights against the
         // plans below: 8-bit 1024 x 4096 x 4096 13 % faster, 1024 x 4096 x 12288

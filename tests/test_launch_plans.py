@@ -75,3 +75,14 @@ def test_gemm_scratch_fits_the_workspace(plans):
     (44, 37888, 12288, 4, True, 146.0, 55.0), (40, 20480, 3072, 8, False, 31.6, 23.3)])
 def test_few_rows_take_the_faster_kernel(plans, M, N, K, bits, frag, streamed, tiled):
     assert (gemm(plans, M, N, K, bits, frag)["cfg"] in STREAM) == (streamed < tiled)
+
+
+# The same for the tiles in k groups and the plans without them
+@pytest.mark.parametrize("M,N,K,bits,frag,without,groups", [
+    (128, 128, 64, 4, True, 3.0, 3.8), (200, 8192, 512, 4, False, 5.1, 6.1), (250, 8192, 512, 8, False, 5.7, 6.4),
+    (57, 14336, 256, 4, True, 4.0, 4.8), (600, 3072, 2048, 4, True, 9.3, 9.8), (64, 2048, 9216, 8, False, 13.1, 16.6),
+    (64, 64, 65536, 4, True, 17.4, 28.7), (64, 8, 65536, 8, True, 16.7, 44.1), (250, 64, 65536, 8, False, 19.3, 60.6),
+    (128, 4096, 4096, 4, True, 12.5, 7.1), (50, 3584, 18944, 4, True, 17.7, 15.2), (100, 1024, 9216, 8, True, 15.2, 11.0),
+    (128, 512, 512, 4, True, 3.86, 3.85), (512, 3584, 18944, 8, True, 96.4, 71.1), (300, 10240, 3072, 8, True, 23.8, 20.1)])
+def test_small_grids_take_the_faster_tiles(plans, M, N, K, bits, frag, without, groups):
+    assert (gemm(plans, M, N, K, bits, frag)["cfg"] in K_GROUPS) == (groups < without)
