@@ -30,6 +30,7 @@
 // x 12288 2155 -> 1996.  Reading both halves of a cache line together where one step
 // takes half of it: 4096 x 12288 1954 -> 1863, 16384 x 3584 711 -> 684.
 #include "tile_common.hpp"
+#include "transform_plan.hpp"
 
 namespace sq {
 namespace {
@@ -59,8 +60,8 @@ __global__ __launch_bounds__(256) void split_basis_kernel(const float* __restric
 }
 
 // KG > 1: KG sets of WM x WN waves share the tile and take turns over its k
-// steps; their sums meet in LDS.
-template <int WM, int WN, int TM, int TN, int KG>
+// steps; their sums meet in LDS.  PAIR: the copies of two steps go out together.
+template <int WM, int WN, int TM, int TN, int KG, bool PAIR>
 __global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_eu(2))) void transform_mfma_kernel(
     const uint16_t* __restrict__ X, const uint8_t* __restrict__ state, const uint16_t* __restrict__ Ps, int M, int K,
     int dm, int du, float* __restrict__ Xp) {
@@ -72,8 +73,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG) __attribute__((amdgpu_waves_per_
     constexpr int CA = AB / 1024, CB = BB / 1024, CN = CA + 2 * CB, NC = CN / NW;
     static_assert(NC * NW == CN && CA % NW == 0, "stage copies must divide evenly, x and Ps apart");
     // A step takes 64 bytes of a row, half a cache line.  With k groups the two halves
-    // are requested together; without, the copies of two steps go out together.
-    constexpr bool PAIR = KG == 1;
+    // are requested together; without, PAIR does it, for a fourth stage of LDS.
     constexpr int NS = PAIR ? 4 : 3;                     // LDS stages
     extern __shared__ __attribute__((aligned(16))) uint8_t sm[];
 
@@ -269,54 +269,39 @@ hipError_t launch_split_basis(const float* P, int K, uint16_t* Ps, hipStream_t s
 
 namespace {
 
-template <int WM, int WN, int TM, int TN, int KG>
+template <int WM, int WN, int TM, int TN, int KG, bool PAIR = KG == 1>
 hipError_t launch_mfma(const uint16_t* X, const uint8_t* state, const uint16_t* Ps, int M, int K, int dm, int du,
                        float* Xp, hipStream_t st) {
-    constexpr int BM = 16 * WM * TM, BN = 16 * WN * TN, LDS = (KG == 1 ? 4 : 3) * KG * (BM + 2 * BN) * kKStep;
+    constexpr int BM = 16 * WM * TM, BN = 16 * WN * TN, LDS = (PAIR ? 4 : 3) * KG * (BM + 2 * BN) * kKStep;
     static_assert(LDS <= 160 * 1024, "the stages fit in LDS");
     const size_t tiles = (size_t)((M + BM - 1) / BM) * (size_t)((K + BN - 1) / BN);
     if (tiles > 0x7fffffffu) return hipErrorInvalidConfiguration;
     static std::atomic<int> lds_set[kMaxDevices];
     const hipError_t attr = allow_dynamic_lds(
-        reinterpret_cast<const void*>(&transform_mfma_kernel<WM, WN, TM, TN, KG>), LDS, lds_set);
+        reinterpret_cast<const void*>(&transform_mfma_kernel<WM, WN, TM, TN, KG, PAIR>), LDS, lds_set);
     if (attr != hipSuccess) return attr;
-    hipLaunchKernelGGL((transform_mfma_kernel<WM, WN, TM, TN, KG>), dim3((unsigned)tiles), dim3(64 * WM * WN * KG), LDS,
-                       st, X, state, Ps, M, K, dm, du, Xp);
+    hipLaunchKernelGGL((transform_mfma_kernel<WM, WN, TM, TN, KG, PAIR>), dim3((unsigned)tiles),
+                       dim3(64 * WM * WN * KG), LDS, st, X, state, Ps, M, K, dm, du, Xp);
     return hipGetLastError();
 }
 
 }  // namespace
 
-// Every tile fills most of a CU's LDS, so a launch runs in rounds of 256 workgroups.
-// Up to 128 x 128, the smallest tile that needs one round (waves of 64 x 64 where the
-// tile holds them: 250 x 4096 25.4 us on 64 x 64 tiles of one such wave in four k
-// groups, 29.9 with four waves of 32 x 32; 512 x 4096 37.9 on 128 x 64, 40.9 with
-// waves of 64 x 32): 64 x 4096 15.0 us on 32 x 32 against 19.0 on 32 x 64, 128 x 4096
-// 19.6 on 32 x 64 against 23.5 on 64 x 64, 64 x 12288 135 on 64 x 64 against 148 on
-// 128 x 64, 128 x 12288 166 on 128 x 64 against 214 on 128 x 128.  Up to 32 rows 32 x
-// 32 whatever the grid (reading Ps bounds it, and a taller tile is padding: 16 x 4096
-// 14.4, 20.1 on 64 x 64; 32 x 18944 283, 322); at 64 rows its second round reads X
-// and fills half the chip again (64 x 12288 163, 64 x 18944 384 against 298 on 128 x
-// 128).
-// Past one round, the least of rounds x time of a round, in the ratio 57 : 100 : 140
-// of 128 x 128, 256 x 128 (eight waves of 64 x 64) and 256 x 192 (64 x 96): 1024 x
-// 12288 570 us in 3 rounds, 650 in 2, 505 in 1; 4096 x 12288 2076 in 12, 1939 in 6,
-// 1832 in 4; 4096 x 4096 254 in 4, 209 in 2, 270 in 2; 16384 x 3584 790, 684, 667.
 hipError_t launch_transform_fast(const uint16_t* X, const uint8_t* state, const uint16_t* Ps, int M, int K, int dm,
                                  int du, float* Xp, hipStream_t st) {
-    auto rounds = [&](int bm, int bn) {
-        return ((size_t)((M + bm - 1) / bm) * (size_t)((K + bn - 1) / bn) + 255) / 256;
-    };
-    if (M <= 32 || rounds(32, 32) == 1)
-        return launch_mfma<1, 1, 2, 2, 8>(X, state, Ps, M, K, dm, du, Xp, st);
-    if (rounds(32, 64) == 1) return launch_mfma<1, 2, 2, 2, 4>(X, state, Ps, M, K, dm, du, Xp, st);
-    if (rounds(64, 64) == 1) return launch_mfma<1, 1, 4, 4, 4>(X, state, Ps, M, K, dm, du, Xp, st);
-    if (rounds(128, 64) == 1) return launch_mfma<2, 1, 4, 4, 2>(X, state, Ps, M, K, dm, du, Xp, st);
-    if (rounds(128, 128) == 1) return launch_mfma<1, 2, 8, 4, 2>(X, state, Ps, M, K, dm, du, Xp, st);
-    const size_t t0 = 57 * rounds(128, 128), t1 = 100 * rounds(256, 128), t2 = 140 * rounds(256, 192);
-    if (t0 <= t1 && t0 <= t2) return launch_mfma<1, 2, 8, 4, 2>(X, state, Ps, M, K, dm, du, Xp, st);
-    if (t1 < t2) return launch_mfma<4, 2, 4, 4, 1>(X, state, Ps, M, K, dm, du, Xp, st);
-    return launch_mfma<4, 2, 4, 6, 1>(X, state, Ps, M, K, dm, du, Xp, st);
+    switch (fast_tile(M, K)) {
+        case FastTile::k32x32: return launch_mfma<1, 1, 2, 2, 8>(X, state, Ps, M, K, dm, du, Xp, st);
+        case FastTile::k32x64: return launch_mfma<1, 2, 2, 2, 4>(X, state, Ps, M, K, dm, du, Xp, st);
+        case FastTile::k64x64: return launch_mfma<1, 1, 4, 4, 4>(X, state, Ps, M, K, dm, du, Xp, st);
+        case FastTile::k64x64x4: return launch_mfma<2, 2, 2, 2, 1, false>(X, state, Ps, M, K, dm, du, Xp, st);
+        case FastTile::k64x64x3: return launch_mfma<2, 2, 2, 2, 1>(X, state, Ps, M, K, dm, du, Xp, st);
+        case FastTile::k128x64: return launch_mfma<2, 1, 4, 4, 2>(X, state, Ps, M, K, dm, du, Xp, st);
+        case FastTile::k128x128: return launch_mfma<1, 2, 8, 4, 2>(X, state, Ps, M, K, dm, du, Xp, st);
+        case FastTile::k128x128x2: return launch_mfma<2, 2, 4, 4, 1, false>(X, state, Ps, M, K, dm, du, Xp, st);
+        case FastTile::k256x128: return launch_mfma<4, 2, 4, 4, 1>(X, state, Ps, M, K, dm, du, Xp, st);
+        case FastTile::k256x192: return launch_mfma<4, 2, 4, 6, 1>(X, state, Ps, M, K, dm, du, Xp, st);
+    }
+    return hipErrorInvalidConfiguration;
 }
 
 }  // namespace sq

@@ -11,10 +11,13 @@ from gpu_util import dev, host, say
 pytestmark = pytest.mark.gpu
 
 
-# 32 x 32 (2 k steps for eight groups; 66 steps), 32 x 64, 64 x 64, 128 x 64, 128 x 128
-# in one round, 256 x 128, 256 x 192, 128 x 128 in three rounds, and 64 x 64 at up to 64 rows
+# 32 x 32 (8 and 66 k steps for eight groups), 32 x 64, 64 x 64, 128 x 64, 128 x 128
+# in one round, 256 x 128, 256 x 192, 128 x 128 in three rounds, and 64 x 64 at up to 64
+# rows; the tiles of a shallow K: 64 x 64 four per CU (2, 18 and 34 steps), three per CU (22)
+# and 128 x 128 two per CU
 @pytest.mark.parametrize("M,K", [(3, 64), (49, 2112), (200, 2112), (321, 1600), (500, 2112), (900, 3136), (1100, 3136),
-                                 (2300, 3136), (1025, 9600), (1100, 10048), (41, 9600)])
+                                 (2300, 3136), (1025, 9600), (1100, 10048), (41, 9600), (1001, 576), (701, 1088),
+                                 (2050, 704), (9301, 896), (3, 256)])
 def test_tiles_within_bound(M, K):
     say(f"transform_fast tiles M={M} K={K}")
     rng = np.random.default_rng(M * K)

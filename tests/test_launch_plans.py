@@ -11,15 +11,19 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2606_04945_amd", "csrc")
 SHIM = r"""
 #include "gemm_plan.hpp"
+#include "transform_plan.hpp"
 extern "C" void gemm(int M, int N, int K, int bits, int frag, int* o) {
     const sq::Plan p = sq::gemm_plan(M, N, K, bits, frag != 0);
     const int v[9] = {p.cfg, p.bm, p.bn, p.splits, p.waves, p.kw, p.alds, p.u, p.d};
     for (int i = 0; i < 9; ++i) o[i] = v[i];
 }
+extern "C" int fast_tile(int M, int K) { return (int)sq::fast_tile(M, K); }
 extern "C" size_t gemm_workspace(int M, int N, int K, int bits) { return sq::plan_workspace_bytes(M, N, K, bits); }
 """
 STREAM = (3, 5, 6)                       # weights streamed into registers
 K_GROUPS = (9, 10, 11, 12, 13, 14)       # tiles in k groups
+FAST_TILES = ("32x32", "32x64", "64x64", "64x64 four per CU", "64x64 three per CU", "128x64", "128x128",
+              "128x128 two per CU", "256x128", "256x192")
 
 
 @pytest.fixture(scope="module")
@@ -86,3 +90,16 @@ def test_few_rows_take_the_faster_kernel(plans, M, N, K, bits, frag, streamed, t
     (128, 512, 512, 4, True, 3.86, 3.85), (512, 3584, 18944, 8, True, 96.4, 71.1), (300, 10240, 3072, 8, True, 23.8, 20.1)])
 def test_small_grids_take_the_faster_tiles(plans, M, N, K, bits, frag, without, groups):
     assert (gemm(plans, M, N, K, bits, frag)["cfg"] in K_GROUPS) == (groups < without)
+
+
+# Matrix-core transform: the faster of two tiles, us on it and on the other
+@pytest.mark.parametrize("M,K,tile,us,other", [
+    (16, 64, "64x64 four per CU", 3.4, 4.4), (543, 1024, "64x64", 10.8, 12.1),
+    (1119, 640, "64x64 four per CU", 7.7, 9.2), (1665, 640, "64x64 four per CU", 9.7, 11.2),
+    (3213, 512, "64x64 three per CU", 9.7, 11.1), (4113, 512, "64x64 three per CU", 12.0, 17.2),
+    (1585, 1280, "64x64 three per CU", 20.4, 27.0), (9344, 896, "128x128 two per CU", 38.7, 47.9),
+    (250, 4096, "64x64", 25.4, 29.9), (512, 4096, "128x64", 37.9, 40.9), (1024, 4096, "128x128", 64.0, 78.0),
+    (4096, 4096, "256x128", 209.0, 254.0), (16384, 3584, "256x192", 667.0, 684.0), (64, 4096, "32x32", 15.0, 19.0),
+    (128, 4096, "32x64", 19.6, 23.5), (3404, 3584, "128x128", 166.6, 180.0)])
+def test_fast_transform_takes_the_faster_tile(plans, M, K, tile, us, other):
+    assert us < other and FAST_TILES[plans.fast_tile(M, K)] == tile
