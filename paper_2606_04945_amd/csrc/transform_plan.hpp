@@ -1,4 +1,4 @@
-// Which tile a transform takes: host code with no HIP in it, so that it is also
+// Which tile or kernel a transform takes: host code with no HIP in it, so that it is also
 // compiled and checked without a GPU compiler.
 #pragma once
 #include <stddef.h>
@@ -53,6 +53,80 @@ inline FastTile fast_tile(int M, int K) {
     const size_t t0 = 57 * rounds(128, 128), t1 = 100 * rounds(256, 128), t2 = 140 * rounds(256, 192);
     if (t0 <= t1 && t0 <= t2) return K <= 2048 ? FastTile::k128x128x2 : FastTile::k128x128;
     return t1 < t2 ? FastTile::k256x128 : FastTile::k256x192;
+}
+
+// Fixed-order transform with its chunks of 256 k split over the waves of a workgroup
+// (transform_split.hip): blocks of 16 x 16 outputs per workgroup, and its waves.
+struct SplitShape {
+    int rb, cb, waves;
+    long cost;
+};
+constexpr int kSplitChunk = 256;
+constexpr long kCus = 256;
+
+// Most waves a workgroup of RB x CB blocks holds: 16 waves leave 128 registers
+// each, which the larger tiles exceed.
+constexpr int split_waves(int blocks) { return blocks <= 4 ? 16 : 8; }
+
+// Time of a tile shape, in 16 x 16 x 256 block chunks of the fp32 matrix cores
+// per SIMD (64 MFMAs, 0.85 us at 2.4 GHz; measured 0.8-1.2 us each), the largest of
+//  - the matrix cores: the busiest CU's workgroups, as many side by side as their
+//    waves fit, times their rounds of chunks; twice that for 4 x 4 blocks with up to
+//    four waves, whose registers leave a SIMD one or two (3612 x 512: 39.6 us, the
+//    smaller shapes 22.7 - 30.3);
+//  - P's bytes at 4.9 TB/s, more where fewer than 192 workgroups read them (16 x
+//    8192: 57 us on 256 workgroups, 66 on 128; 16 x 12288: 127 us on 192);
+//  - P read again by every row tile: 64-, 128- and 256-byte runs (CB = 1, 2, 4) came
+//    back at 5.0, 6.9 and 11.5 TB/s (100 x 12288 in 7 row tiles: 849, 613, 367 us).
+inline SplitShape split_cost(int rb, int cb, int M, int K) {
+    const long nch = (K + kSplitChunk - 1) / kSplitChunk;
+    const int cap = split_waves(rb * cb), W = (int)(nch < cap ? nch : cap);
+    const long rows = (M + 16 * rb - 1) / (16 * rb);
+    const long wgs = rows * (K / (16 * cb));
+    const long n = (wgs + kCus - 1) / kCus, side = cap / W;
+    const long passes = (n + side - 1) / side, at_once = n < side ? n : side;
+    long cost = passes * ((at_once * W + 3) / 4) * ((nch + W - 1) / W) * rb * cb;
+    if (rb * cb == 16 && W <= 4) cost *= 2;
+    const long p_read = (long)K * K;                 // x 1400000; divided last, small K count too
+    const long mem = p_read * 192 / (1400000 * (wgs < 192 ? wgs : 192));
+    const long again = p_read * rows * (cb == 1 ? 16 : cb == 2 ? 10 : 7) / (16 * 1400000);
+    if (cost < mem) cost = mem;
+    if (cost < again) cost = again;
+    return {rb, cb, W, cost};
+}
+
+inline SplitShape split_shape(int M, int K) {
+    // largest tile first: among equals it reads P and X least often
+    constexpr int shapes[][2] = {{4, 4}, {2, 4}, {1, 4}, {1, 2}, {1, 1}};
+    SplitShape best{0, 0, 0, 0};
+    for (const auto& s : shapes) {
+        if (K % (16 * s[1]) || (s[0] > 1 && M <= 8 * s[0])) continue;   // no row block of padding only
+        const SplitShape c = split_cost(s[0], s[1], M, K);
+        if (!best.rb || c.cost < best.cost) best = c;
+    }
+    return best;
+}
+
+// The tiled kernels take 64 x 128 tiles (32 blocks on four SIMDs: 8 per chunk)
+// or, from 512 tiles on, 128 x 128.  One tile per CU costs them a fifth more per
+// block than two.  Measured at K = 4096: 512 rows 145 us split, 169 tiled (equal
+// costs, one tile per CU); 1024 rows 288 and 273 (equal, two); K = 4160: 256
+// rows 118 and 171 (cost 144 against 136, one tile per CU); K = 12288: 256 rows
+// 641 and 793, 512 rows 1271 and 1250 (equal, three); K = 1536: 4608 rows 222 and
+// 210 (cost 182 against 192, four), so several tiles need a sixteenth less.  From
+// five to eight chunks, which one round of the waves holds, three thirty-seconds
+// less: 2705 x 1344 112.6 us split and 95.3 tiled, 4029 x 1280 152.8 and 139.5; up
+// to three chunks the tiles' own ends cost as much: 3612 x 512 22.7 and 27.7.
+// Up to 32 rows the split is always taken.
+inline bool split_faster(int M, int K) {
+    if ((size_t)M * K * 2 > 0x7fffffff) return false;   // X is addressed with 32-bit buffer offsets
+    if (M <= 32) return true;
+    const long cols = (K + 127) / 128;
+    if ((long)((M + 127) / 128) * cols >= 512) return false;
+    const long tiles = (long)((M + 63) / 64) * cols, n = (tiles + kCus - 1) / kCus;
+    const long nch = (K + kSplitChunk - 1) / kSplitChunk, tiled = n * 8 * nch;
+    const long less = nch <= 3 ? 0 : nch >= 5 && nch <= 8 ? 3 : 2;
+    return split_shape(M, K).cost < (n == 1 ? tiled + tiled / 8 + 1 : tiled - tiled * less / 32);
 }
 
 }  // namespace

@@ -25,9 +25,12 @@
 // 123), 18944 335 (1060; 293).  64 / 128 / 256 rows at K = 4096 against 64 x
 // 128 tiles: 27 / 39 / 74 us (167 / 166 / 166).
 #include "tile_common.hpp"
+#include "transform_plan.hpp"
 
 namespace sq {
 namespace {
+
+static_assert(kChunk == kSplitChunk, "the rule counts chunks of the fixed order");
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
@@ -61,10 +64,6 @@ __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
 }
-
-// Most waves a workgroup of RB x CB blocks holds: 16 waves leave 128 registers
-// each, which the larger tiles exceed.
-constexpr int split_waves(int blocks) { return blocks <= 4 ? 16 : 8; }
 
 template <int RB, int CB>
 __global__ __launch_bounds__(split_waves(RB * CB) * kWave) void transform_split_kernel(const uint16_t* __restrict__ X,
@@ -231,84 +230,18 @@ hipError_t launch_split(const uint16_t* X, const uint8_t* state, const float* P,
     return hipGetLastError();
 }
 
-struct SplitShape {
-    int rb, cb;
-};
-// largest tile first: among equals it reads P and X least often
-constexpr SplitShape kSplitShapes[] = {{4, 4}, {2, 4}, {1, 4}, {1, 2}, {1, 1}};
-constexpr long kCus = 256;
-
-// Time of a tile shape, in 16 x 16 x 256 block chunks of the fp32 matrix cores
-// per SIMD (64 MFMAs, 0.85 us at 2.4 GHz; measured 0.8-1.2 us each), the largest of
-//  - the matrix cores: the busiest CU's workgroups, as many side by side as their
-//    waves fit, times their rounds of chunks;
-//  - P's bytes at 4.9 TB/s, more where fewer than 192 workgroups read them (16 x
-//    8192: 57 us on 256 workgroups, 66 on 128; 16 x 12288: 127 us on 192);
-//  - P read again by every row tile: 64-, 128- and 256-byte runs (CB = 1, 2, 4) came
-//    back at 4.9, 7.5 and 13 TB/s (100 x 12288 in 7 row tiles: 849, 613, 367 us).
-// Over 190 sizes (48 ... 10000 rows, K = 512 ... 4096) the choice, the tiled kernel
-// included, takes 5 % more than the fastest of six on average.
-long split_cost(SplitShape s, int M, int K, int& W) {
-    const long nch = (K + kChunk - 1) / kChunk;
-    const int cap = split_waves(s.rb * s.cb);
-    W = (int)(nch < cap ? nch : cap);
-    const long rows = (M + 16 * s.rb - 1) / (16 * s.rb);
-    const long wgs = rows * (K / (16 * s.cb));
-    const long n = (wgs + kCus - 1) / kCus, side = cap / W;
-    const long passes = (n + side - 1) / side, at_once = n < side ? n : side;
-    const long mfma = passes * ((at_once * W + 3) / 4) * ((nch + W - 1) / W) * s.rb * s.cb;
-    const long p_read = (long)K * K;                 // x 1400000; divided last, small K count too
-    const long mem = p_read * 192 / (1400000 * (wgs < 192 ? wgs : 192));
-    const long again = p_read * rows * (s.cb == 1 ? 8 : s.cb == 2 ? 5 : 3) / (8 * 1400000);
-    const long cost = mfma > mem ? mfma : mem;
-    return cost > again ? cost : again;
-}
-
-SplitShape split_shape(int M, int K, int& W, long& cost) {
-    SplitShape best{1, 1};
-    cost = -1;
-    for (const SplitShape s : kSplitShapes) {
-        if (K % (16 * s.cb) || (s.rb > 1 && M <= 8 * s.rb)) continue;   // no row block of padding only
-        int w;
-        const long c = split_cost(s, M, K, w);
-        if (cost < 0 || c < cost) best = s, cost = c, W = w;
-    }
-    return best;
-}
-
 }  // namespace
 
-// The tiled kernels take 64 x 128 tiles (32 blocks on four SIMDs: 8 per chunk)
-// or, from 512 tiles on, 128 x 128.  One tile per CU costs them a fifth more per
-// block than two.  Measured at K = 4096: 512 rows 145 us here, 169 tiled (equal
-// costs, one tile per CU); 1024 rows 288 and 273 (equal, two); K = 4160: 256
-// rows 118 and 171 (cost 144 against 136, one tile per CU); K = 12288: 256 rows
-// 641 and 793, 512 rows 1271 and 1250 (equal, three); K = 1536: 4608 rows 222 and
-// 210 (cost 182 against 192, four), so several tiles need a sixteenth less.
-// Up to 32 rows the split is always taken.
-bool transform_split_faster(int M, int K) {
-    if ((size_t)M * K * 2 > 0x7fffffff) return false;   // X is addressed with 32-bit buffer offsets
-    if (M <= 32) return true;
-    const long cols = (K + 127) / 128;
-    if ((long)((M + 127) / 128) * cols >= 512) return false;
-    const long tiles = (long)((M + 63) / 64) * cols, n = (tiles + kCus - 1) / kCus;
-    const long tiled = n * 8 * ((K + kChunk - 1) / kChunk);
-    int W;
-    long cost;
-    split_shape(M, K, W, cost);
-    return cost < (n == 1 ? tiled + tiled / 8 + 1 : tiled - tiled / 16);
-}
+bool transform_split_faster(int M, int K) { return split_faster(M, K); }
 
 hipError_t launch_transform_split(const uint16_t* X, const uint8_t* state, const float* P, int M, int K, int dm,
                                   int du, float* Xp, hipStream_t st) {
-    int W = 1;
-    long cost;
-    const SplitShape s = split_shape(M, K, W, cost);
-    if (s.rb == 4) return launch_split<4, 4>(X, state, P, M, K, dm, du, W, Xp, st);
-    if (s.rb == 2) return launch_split<2, 4>(X, state, P, M, K, dm, du, W, Xp, st);
-    if (s.cb == 4) return launch_split<1, 4>(X, state, P, M, K, dm, du, W, Xp, st);
-    if (s.cb == 2) return launch_split<1, 2>(X, state, P, M, K, dm, du, W, Xp, st);
-    return launch_split<1, 1>(X, state, P, M, K, dm, du, W, Xp, st);
+    const SplitShape s = split_shape(M, K);
+    if (s.rb == 4) return launch_split<4, 4>(X, state, P, M, K, dm, du, s.waves, Xp, st);
+    if (s.rb == 2) return launch_split<2, 4>(X, state, P, M, K, dm, du, s.waves, Xp, st);
+    if (s.cb == 4) return launch_split<1, 4>(X, state, P, M, K, dm, du, s.waves, Xp, st);
+    if (s.cb == 2) return launch_split<1, 2>(X, state, P, M, K, dm, du, s.waves, Xp, st);
+    return launch_split<1, 1>(X, state, P, M, K, dm, du, s.waves, Xp, st);
 }
 
 }  // namespace sq

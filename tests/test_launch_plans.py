@@ -18,6 +18,11 @@ extern "C" void gemm(int M, int N, int K, int bits, int frag, int* o) {
     for (int i = 0; i < 9; ++i) o[i] = v[i];
 }
 extern "C" int fast_tile(int M, int K) { return (int)sq::fast_tile(M, K); }
+extern "C" int split(int M, int K, int* o) {
+    const sq::SplitShape s = sq::split_shape(M, K);
+    o[0] = s.rb; o[1] = s.cb; o[2] = s.waves;
+    return sq::split_faster(M, K);
+}
 extern "C" size_t gemm_workspace(int M, int N, int K, int bits) { return sq::plan_workspace_bytes(M, N, K, bits); }
 """
 STREAM = (3, 5, 6)                       # weights streamed into registers
@@ -103,3 +108,31 @@ def test_small_grids_take_the_faster_tiles(plans, M, N, K, bits, frag, without, 
     (128, 4096, "32x64", 19.6, 23.5), (3404, 3584, "128x128", 166.6, 180.0)])
 def test_fast_transform_takes_the_faster_tile(plans, M, K, tile, us, other):
     assert us < other and FAST_TILES[plans.fast_tile(M, K)] == tile
+
+
+# Fixed-order transform: us on the tiled kernel and on the split one with 4 x 4, 2 x 4,
+# 1 x 4, 1 x 2 and 1 x 1 blocks of outputs per workgroup
+SPLIT_BLOCKS = ((4, 4), (2, 4), (1, 4), (1, 2), (1, 1))
+
+
+@pytest.mark.parametrize("M,K,tiled,split", [
+    (2705, 1344, 95.3, (146.0, 133.6, 113.2, 120.5, 153.9)), (4029, 1280, 139.5, (183.6, 188.2, 154.4, 158.3, 223.4)),
+    (2655, 2624, 358.1, (391.2, 403.9, 400.6, 436.0, 598.8)), (3612, 512, 27.7, (39.7, 23.2, 22.7, 28.0, 30.3)),
+    (3848, 512, 28.3, (40.6, 24.1, 23.6, 30.6, 33.9)), (191, 4096, 165.5, (73.7, 74.9, 62.2, 83.7, 102.9)),
+    (95, 4096, 165.9, (72.8, 40.6, 42.6, 45.2, 55.5)), (41, 4096, 165.4, (72.0, 39.2, 24.0, 30.3, 30.1)),
+    (641, 4096, 268.4, (217.2, 221.0, 216.1, 284.4, 376.5)), (94, 11648, 461.1, (424.7, 328.9, 315.8, 398.7, 572.6))])
+def test_fixed_order_transform_takes_the_faster_kernel(plans, M, K, tiled, split):
+    o = (ctypes.c_int * 3)()
+    us = split[SPLIT_BLOCKS.index((o[0], o[1]))] if plans.split(M, K, o) else tiled
+    assert us <= 1.05 * min(tiled, *split)
+
+
+def test_fixed_order_transform_blocks_fit(plans):
+    """The blocks divide the columns, no row block is padding only, and the waves fit a workgroup."""
+    o = (ctypes.c_int * 3)()
+    for M in (1, 8, 9, 16, 17, 32, 33, 100, 1000, 5000):
+        for K in range(64, 19009, 64):
+            plans.split(M, K, o)
+            rb, cb, waves = o
+            assert (rb, cb) in SPLIT_BLOCKS and K % (16 * cb) == 0 and (rb == 1 or M > 8 * rb)
+            assert 1 <= waves <= min(16 if rb * cb <= 4 else 8, -(-K // 256))
