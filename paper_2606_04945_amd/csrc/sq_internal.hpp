@@ -150,7 +150,7 @@ hipError_t launch_transform(const uint16_t* X, const uint8_t* state, const float
 
 // The same with k split over the waves of a workgroup (transform_split.hip), for
 // few rows: whether that is the faster form, and its launch (P given, X under 2 GiB).
-bool transform_split_faster(int M, int K);
+bool transform_split_faster(int M, int K, int dm, int du, bool gated);
 hipError_t launch_transform_split(const uint16_t* X, const uint8_t* state, const float* P, int M, int K, int dm,
                                   int du, float* Xp, hipStream_t st);
 

@@ -286,7 +286,8 @@ hipError_t launch_transform(const uint16_t* X, const uint8_t* state, const float
         hipLaunchKernelGGL(gate_copy_kernel, dim3(blocks), dim3(kThreads), 0, st, X, state, M, K, dm, du, Xp);
         return hipGetLastError();
     }
-    if (transform_split_faster(M, K)) return launch_transform_split(X, state, P, M, K, dm, du, Xp, st);
+    if (transform_split_faster(M, K, dm, du, state != nullptr))
+        return launch_transform_split(X, state, P, M, K, dm, du, Xp, st);
     // The pipelined kernel addresses X with 32-bit buffer offsets, so a call whose
     // X exceeds 2 GiB runs as independent chunks of rows (rows never interact).
     const int Mc = (int)(((size_t)0x7fffffff / ((size_t)K * 2)) / 128 * 128);

@@ -118,12 +118,28 @@ inline SplitShape split_shape(int M, int K) {
 // less: 2705 x 1344 112.6 us split and 95.3 tiled, 4029 x 1280 152.8 and 139.5; up
 // to three chunks the tiles' own ends cost as much: 3612 x 512 22.7 and 27.7.
 // Up to 32 rows the split is always taken.
-inline bool split_faster(int M, int K) {
+// With a state per row the tiled kernel groups the rows by it and skips the column
+// tiles that lie wholly in a row's zeroed band, here taken as half of the rows on
+// either side; the split kernel reads all of K.  384 x 12288 with two bands of 6016
+// 785 us tiled and 979 split, 901 x 6784 with two of 3328 448 and 783, 1703 x 4032
+// with one of 3870 203 and 509.  At up to two tiles per CU the gain goes into waiting
+// for the fullest CU: those calls are judged without it (384 x 12288 with two bands
+// of 384 fills three, of which 34 tiles in 576 are skipped: 978 split, 1242 tiled).
+inline bool split_faster(int M, int K, int dm, int du, bool gated) {
     if ((size_t)M * K * 2 > 0x7fffffff) return false;   // X is addressed with 32-bit buffer offsets
     if (M <= 32) return true;
     const long cols = (K + 127) / 128;
     if ((long)((M + 127) / 128) * cols >= 512) return false;
-    const long tiles = (long)((M + 63) / 64) * cols, n = (tiles + kCus - 1) / kCus;
+    const long rows = (M + 63) / 64;
+    long n = (rows * cols + kCus - 1) / kCus;
+    if (gated && n > 2) {
+        const long u0 = K - du, m0 = u0 - dm;
+        const long skip_u = cols - (u0 + 127) / 128, skip_m = u0 / 128 - (m0 + 127) / 128;
+        const long skip = (skip_u > 0 ? skip_u : 0) + (skip_m > 0 ? skip_m : 0);   // for half of the rows
+        // half a tile per CU more, for the uneven rest
+        const long left = (rows * (2 * cols - skip) + kCus + 2 * kCus - 1) / (2 * kCus);
+        n = left < 2 ? 2 : left < n ? left : n;
+    }
     const long nch = (K + kSplitChunk - 1) / kSplitChunk, tiled = n * 8 * nch;
     const long less = nch <= 3 ? 0 : nch >= 5 && nch <= 8 ? 3 : 2;
     return split_shape(M, K).cost < (n == 1 ? tiled + tiled / 8 + 1 : tiled - tiled * less / 32);

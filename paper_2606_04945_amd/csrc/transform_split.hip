@@ -232,7 +232,7 @@ hipError_t launch_split(const uint16_t* X, const uint8_t* state, const float* P,
 
 }  // namespace
 
-bool transform_split_faster(int M, int K) { return split_faster(M, K); }
+bool transform_split_faster(int M, int K, int dm, int du, bool gated) { return split_faster(M, K, dm, du, gated); }
 
 hipError_t launch_transform_split(const uint16_t* X, const uint8_t* state, const float* P, int M, int K, int dm,
                                   int du, float* Xp, hipStream_t st) {

@@ -18,10 +18,10 @@ extern "C" void gemm(int M, int N, int K, int bits, int frag, int* o) {
     for (int i = 0; i < 9; ++i) o[i] = v[i];
 }
 extern "C" int fast_tile(int M, int K) { return (int)sq::fast_tile(M, K); }
-extern "C" int split(int M, int K, int* o) {
+extern "C" int split(int M, int K, int dm, int du, int gated, int* o) {
     const sq::SplitShape s = sq::split_shape(M, K);
     o[0] = s.rb; o[1] = s.cb; o[2] = s.waves;
-    return sq::split_faster(M, K);
+    return sq::split_faster(M, K, dm, du, gated != 0);
 }
 extern "C" size_t gemm_workspace(int M, int N, int K, int bits) { return sq::plan_workspace_bytes(M, N, K, bits); }
 """
@@ -123,7 +123,7 @@ SPLIT_BLOCKS = ((4, 4), (2, 4), (1, 4), (1, 2), (1, 1))
     (641, 4096, 268.4, (217.2, 221.0, 216.1, 284.4, 376.5)), (94, 11648, 461.1, (424.7, 328.9, 315.8, 398.7, 572.6))])
 def test_fixed_order_transform_takes_the_faster_kernel(plans, M, K, tiled, split):
     o = (ctypes.c_int * 3)()
-    us = split[SPLIT_BLOCKS.index((o[0], o[1]))] if plans.split(M, K, o) else tiled
+    us = split[SPLIT_BLOCKS.index((o[0], o[1]))] if plans.split(M, K, 0, 0, 0, o) else tiled
     assert us <= 1.05 * min(tiled, *split)
 
 
@@ -132,7 +132,17 @@ def test_fixed_order_transform_blocks_fit(plans):
     o = (ctypes.c_int * 3)()
     for M in (1, 8, 9, 16, 17, 32, 33, 100, 1000, 5000):
         for K in range(64, 19009, 64):
-            plans.split(M, K, o)
+            plans.split(M, K, 0, 0, 0, o)
             rb, cb, waves = o
             assert (rb, cb) in SPLIT_BLOCKS and K % (16 * cb) == 0 and (rb == 1 or M > 8 * rb)
             assert 1 <= waves <= min(16 if rb * cb <= 4 else 8, -(-K // 256))
+
+
+# us on the tiled and on the split kernel, half of the rows in either state
+@pytest.mark.parametrize("M,K,dm,du,tiled,split", [
+    (384, 12288, 6016, 6016, 785, 979), (901, 6784, 3328, 3328, 448, 783), (1703, 4032, 0, 3870, 203, 509),
+    (384, 12288, 384, 384, 1242, 978), (384, 12288, 0, 0, 1242, 978), (70, 4544, 760, 760, 184, 50)])
+def test_fixed_order_transform_counts_the_bands(plans, M, K, dm, du, tiled, split):
+    o = (ctypes.c_int * 3)()
+    assert plans.split(M, K, dm, du, 1, o) == (split < tiled)
+    assert plans.split(M, K, dm, du, 0, o) == plans.split(M, K, 0, 0, 1, o) == plans.split(M, K, 0, 0, 0, o)
