@@ -12,6 +12,7 @@
 // accumulators (8 x 4 when g < 8), so each pair of LDS reads feeds 64 (32)
 // fused multiply-adds.
 #include "tile_common.hpp"
+#include "tac_plan.hpp"
 
 namespace sq {
 namespace {
@@ -341,7 +342,6 @@ namespace {
 
 constexpr int kTqMaxConsumerWaves = 8;       // K <= 4096
 constexpr int kTqRing = 6;                   // row slots in the LDS ring
-constexpr int kTqMaxRows = 64;               // rows per workgroup (their states live in LDS)
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 
 // Producer: wait until at most `n` of this wave's ring loads are in flight
@@ -885,14 +885,7 @@ hipError_t launch_tac_quant(const uint16_t* Z, const uint16_t* Mb, const uint16_
                          : launch_tqm<4, 32>(M, Z, Mb, d, state, K, dm, du, Aq, s, st);
     const int cw = (K / 8 + kWave - 1) / kWave;
     const int threads = (cw + 1) * kWave;
-    // about two workgroups per CU, each streaming a run of up to 64 rows; one where
-    // a CU holds only one (g = 16 at K > 3584: nine waves of 124 registers), and up
-    // to 1024 rows at g = 16 and seven waves, where reading the block rows (16 g K
-    // bits per workgroup) weighs most: 1024 x 4096 14.1 -> 11.0 us, 2000 x 4096
-    // 20.6 -> 17.3, 700 x 3584 10.1 -> 8.9 (2000 x 3584 15.4 against 16.4)
-    const int wgs = g == 16 && (cw == 8 || (cw == 7 && M <= 1024)) ? 256 : 512;
-    int rows = (M + wgs - 1) / wgs;
-    rows = rows < 1 ? 1 : (rows > kTqMaxRows ? kTqMaxRows : rows);
+    const int rows = tac_quant_rows(M, K, g);
     const dim3 grid((M + rows - 1) / rows);
     // at most 6 x 8 KB + 128 bytes (K <= 4096): inside the default 64 KB dynamic-LDS limit
     const size_t lds = (size_t)kTqRing * cw * 1024 + 2 * kTqMaxConsumerWaves * sizeof(float) + kTqMaxRows;

@@ -11,6 +11,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2606_04945_amd", "csrc")
 SHIM = r"""
 #include "gemm_plan.hpp"
+#include "tac_plan.hpp"
 #include "transform_plan.hpp"
 extern "C" void gemm(int M, int N, int K, int bits, int frag, int* o) {
     const sq::Plan p = sq::gemm_plan(M, N, K, bits, frag != 0);
@@ -18,6 +19,7 @@ extern "C" void gemm(int M, int N, int K, int bits, int frag, int* o) {
     for (int i = 0; i < 9; ++i) o[i] = v[i];
 }
 extern "C" int fast_tile(int M, int K) { return (int)sq::fast_tile(M, K); }
+extern "C" int tac_quant_rows(int M, int K, int g) { return sq::tac_quant_rows(M, K, g); }
 extern "C" int split(int M, int K, int dm, int du, int gated, int* o) {
     const sq::SplitShape s = sq::split_shape(M, K);
     o[0] = s.rb; o[1] = s.cb; o[2] = s.waves;
@@ -146,3 +148,19 @@ def test_fixed_order_transform_counts_the_bands(plans, M, K, dm, du, tiled, spli
     o = (ctypes.c_int * 3)()
     assert plans.split(M, K, dm, du, 1, o) == (split < tiled)
     assert plans.split(M, K, dm, du, 0, o) == plans.split(M, K, 0, 0, 1, o) == plans.split(M, K, 0, 0, 0, o)
+
+
+# Fused calibration + quantisation at g = 16: us with 256 and with 512 workgroups
+@pytest.mark.parametrize("M,K,us256,us512", [
+    (513, 3584, 9.21, 8.67), (514, 3584, 9.16, 9.98), (700, 3584, 9.39, 10.58), (768, 3584, 9.41, 10.61),
+    (800, 3584, 10.93, 10.71), (1000, 3328, 11.10, 10.93), (513, 4096, 9.47, 11.58), (1024, 4096, 11.0, 14.1),
+    (2000, 4096, 17.3, 20.6), (2000, 3584, 16.4, 15.4)])
+def test_tac_quantiser_takes_the_faster_grid(plans, M, K, us256, us512):
+    assert plans.tac_quant_rows(M, K, 16) == -(-M // (256 if us256 < us512 else 512))
+
+
+def test_tac_quantiser_rows_in_range(plans):
+    for M in (0, 1, 2, 255, 256, 257, 512, 4095, 16384, 16385, 32768, 32769, 1 << 24):
+        for K in (16, 512, 3520, 3584, 3648, 4096):
+            for g in (1, 8, 16):
+                assert 1 <= plans.tac_quant_rows(M, K, g) <= 64
