@@ -20,9 +20,10 @@
 // one barrier per step.  LDS rows are XOR-swizzled by 16-byte chunk so the
 // fragment reads are free of bank conflicts; each wave unpacks the fragments it
 // reads.  Rows past M (or N) and the unused half of a last k step read as zero
-// through the buffer descriptors' range check.  Few tiles (M of 17 to a few
-// hundred) split K across workgroups; the int32 partial sums are then added
-// exactly by a small kernel.
+// through the buffer descriptors' range check.  Small grids (17 to a few hundred
+// rows) share a tile's K among groups of waves of one workgroup; the few of them
+// whose K is deep for that split it across workgroups, and the int32 partial sums
+// are then added exactly by a small kernel.
 // Few rows (M <= 16, some shapes up to 48) have kernels of their own that stream
 // the weights into registers.
 //
@@ -741,7 +742,7 @@ hipError_t launch_tiled(const Plan& p, const uint8_t* Aq, const float* s_a, cons
     if (p.splits == 1) {
         hipLaunchKernelGGL((gemm_tile_kernel<WM, WN, TM, TN, false, BITS, OCC, WF, KG>), grid, block, 0, st, Aq, s_a,
                            Wq, s_w, M, N, K, p.per, Y, acc, (int32_t*)nullptr);
-    } else if constexpr (KG == 1) {
+    } else if constexpr (WM * TM == 4 && WN * TN == 4 && KG == 1) {   // only 64 x 64 tiles split K
         hipLaunchKernelGGL((gemm_tile_kernel<WM, WN, TM, TN, true, BITS, OCC, WF>), grid, block, 0, st, Aq, s_a, Wq,
                            s_w, M, N, K, p.per, (uint16_t*)nullptr, (int32_t*)nullptr, part);
     } else {
@@ -776,16 +777,19 @@ hipError_t launch_short_frag_tm(const Plan& p, const uint8_t* Aq, const float* s
             case 5: return launch_short_frag_t<TM, 1, true, 1, 4, BITS>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, st);
             case 6: return launch_short_frag_t<TM, 1, true, 2, 4, BITS>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, st);
             case 9: return launch_short_frag_t<TM, 2, true, 1, 4, BITS>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, st);
-            case 10: return launch_short_frag_t<TM, 2, true, 2, 4, BITS>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, st);
+            case 10:   // three row tiles of 4-bit codes: staged up to eight k steps only
+                if constexpr (TM < 3 || BITS == 8)
+                    return launch_short_frag_t<TM, 2, true, 2, 4, BITS>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, st);
+                return hipErrorInvalidConfiguration;
             default: return hipErrorInvalidConfiguration;
         }
     }
     if (p.u != 2) return hipErrorInvalidConfiguration;
+    constexpr int D4 = TM > 1 ? 2 : 4;   // ring of the four-wave form
     switch (p.kw * 8 + p.d) {
         case 12: return launch_short_frag_t<TM, 1, false, 2, 4, BITS>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, st);
         case 20: return launch_short_frag_t<TM, 2, false, 2, 4, BITS>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, st);
-        case 34: return launch_short_frag_t<TM, 4, false, 2, 2, BITS>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, st);
-        case 36: return launch_short_frag_t<TM, 4, false, 2, 4, BITS>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, st);
+        case 32 + D4: return launch_short_frag_t<TM, 4, false, 2, D4, BITS>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, st);
         default: return hipErrorInvalidConfiguration;
     }
 }
@@ -874,7 +878,7 @@ hipError_t launch_gemm_frag(const uint8_t* Aq, const float* s_a, const uint8_t* 
             case 8: e = launch_tiled<1, 2, 8, 4, 8, 2, true>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, part, st); break;
             case 1: e = launch_tiled<2, 2, 4, 4, 8, 3, true>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, part, st); break;
             case 2: e = launch_tiled<2, 2, 2, 2, 8, 4, true>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, part, st); break;
-            default: e = launch_tiled<1, 4, 4, 2, 8, 4, true>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, part, st); break;
+            default: return hipErrorInvalidConfiguration;
         }
     } else {
         switch (p.cfg) {
@@ -887,7 +891,8 @@ hipError_t launch_gemm_frag(const uint8_t* Aq, const float* s_a, const uint8_t* 
             case 14: e = launch_tiled<1, 4, 4, 2, 4, 2, true, 3>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, part, st); break;
             case 1: e = launch_tiled<2, 2, 4, 4, 4, 3, true>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, part, st); break;
             case 2: e = launch_tiled<2, 2, 2, 2, 4, 4, true>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, part, st); break;
-            default: e = launch_tiled<1, 4, 4, 2, 4, 4, true>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, part, st); break;
+            case 4: e = launch_tiled<1, 4, 4, 2, 4, 4, true>(p, Aq, s_a, Wf, s_w, M, N, K, Y, acc, part, st); break;
+            default: return hipErrorInvalidConfiguration;
         }
     }
     if (e != hipSuccess) return e;
@@ -914,7 +919,7 @@ hipError_t launch_gemm(const uint8_t* Aq, const float* s_a, const uint8_t* Wq, c
             case 8: e = launch_tiled<1, 2, 8, 4, 8, 2>(p, Aq, s_a, Wq, s_w, M, N, K, Y, acc, part, st); break;
             case 1: e = launch_tiled<2, 2, 4, 4, 8, 3>(p, Aq, s_a, Wq, s_w, M, N, K, Y, acc, part, st); break;
             case 2: e = launch_tiled<2, 2, 2, 2, 8, 4>(p, Aq, s_a, Wq, s_w, M, N, K, Y, acc, part, st); break;
-            default: e = launch_tiled<1, 4, 4, 2, 8, 4>(p, Aq, s_a, Wq, s_w, M, N, K, Y, acc, part, st); break;
+            default: return hipErrorInvalidConfiguration;
         }
     } else {
         switch (p.cfg) {
@@ -929,7 +934,8 @@ hipError_t launch_gemm(const uint8_t* Aq, const float* s_a, const uint8_t* Wq, c
             case 14: e = launch_tiled<1, 4, 4, 2, 4, 2, false, 3>(p, Aq, s_a, Wq, s_w, M, N, K, Y, acc, part, st); break;
             case 1: e = launch_tiled<2, 2, 4, 4, 4, 3>(p, Aq, s_a, Wq, s_w, M, N, K, Y, acc, part, st); break;
             case 2: e = launch_tiled<2, 2, 2, 2, 4, 4>(p, Aq, s_a, Wq, s_w, M, N, K, Y, acc, part, st); break;
-            default: e = launch_tiled<1, 4, 4, 2, 4, 4>(p, Aq, s_a, Wq, s_w, M, N, K, Y, acc, part, st); break;
+            case 4: e = launch_tiled<1, 4, 4, 2, 4, 4>(p, Aq, s_a, Wq, s_w, M, N, K, Y, acc, part, st); break;
+            default: return hipErrorInvalidConfiguration;
         }
     }
     if (e != hipSuccess) return e;

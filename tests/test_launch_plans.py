@@ -7,6 +7,8 @@ import subprocess
 
 import pytest
 
+from gemm_kernels import KERNELS, kernel_of
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2606_04945_amd", "csrc")
 SHIM = r"""
@@ -61,6 +63,21 @@ def shapes(n, seed):
         bits = rng.choice((4, 8))
         yield (log_uniform(rng, 1, 4096), 8 * log_uniform(rng, 1, 8192),
                64 * log_uniform(rng, 1, 1024 if bits == 8 else 2048), bits)
+
+
+def test_every_gemm_kernel_is_reached(plans):
+    for name, (M, N, K) in KERNELS.items():
+        bits, frag = int(name[0]), "fragments" in name
+        assert kernel_of(gemm(plans, M, N, K, bits, frag), M, bits, frag) == name
+
+
+def test_no_plan_asks_for_another_gemm_kernel(plans):
+    few = [(M, 16 * g - 8, 64 * k, bits) for M in (1, 16, 17, 32, 33, 36, 40, 48)
+           for g in (1, 128, 256, 257, 384, 512, 513, 768, 1023, 1024, 1025, 2400)
+           for k in (*range(1, 50), *range(60, 130, 3), 160, 300, 1024) for bits in (4, 8)]
+    for M, N, K, bits in (*few, *shapes(50000, 2)):
+        for frag in (False, True):
+            assert kernel_of(gemm(plans, M, N, K, bits, frag), M, bits, frag) in KERNELS, (M, N, K)
 
 
 def test_gemm_scratch_fits_the_workspace(plans):
