@@ -5,8 +5,8 @@
 * the GEMM on weights the oracle reordered (so independent of the GPU
   converter) gives the oracle's int32 accumulators and fp16 outputs bit for bit;
 * on GPU-converted weights, at every short-M plan (wide, mid-width and narrow
-  layers; activations staged in LDS or read from L2; one to four row tiles),
-  every tiled plan (with and without K splits; 64 x 64 ... 128 x 256 tiles; k
+  layers; activations staged in LDS or read from L2; one to three row tiles),
+  every tiled plan (with and without K splits; 32 x 32 ... 128 x 256 tiles; k
   groups within a workgroup) and at the largest K with the
   extreme sum 2^23, acc and Y equal the oracle's and w4a4_gemm's;
 * the same for int8 codes (W8A8): conversion, GEMM on oracle-ordered weights,
@@ -48,20 +48,21 @@ def test_gemm_on_oracle_ordered_weights():
 
 
 SHAPES = [
-    # short M: wide (>= 1024 column groups), mid-width, narrow; LDS or L2 activations
+    # short M: wide (>= 1024 column groups), mid-width, narrow; LDS or L2 activations (from
+    # 17 rows the mid-width layers and those whose activations do not fit take tiles)
     (1, 24576, 4096), (16, 24576, 4096), (32, 24576, 4096), (48, 24576, 4096), (33, 37888, 3584),
     (16, 12288, 4096), (17, 12296, 4160), (48, 8200, 12288),
     (1, 4096, 4096), (16, 4096, 12288), (5, 4104, 4160), (48, 3584, 18944), (1, 8, 64), (3, 24, 192),
     (3, 16392, 8192), (40, 16392, 8192),
     # one k step per batch where two would leave zero-weight steps; the two-batch ring of narrow
-    # layers at two or three row tiles; activations from L2 where they do not fit in LDS; short K
+    # layers at two row tiles; activations from L2 where they do not fit in LDS; short K
     (1, 37888, 3584), (32, 37888, 3584), (16, 8192, 2560), (40, 8192, 2560), (32, 12288, 4096),
     (16, 4608, 3584), (48, 4608, 3584), (32, 4096, 4096), (20, 16392, 12288), (32, 8200, 12288),
     (16, 4096, 1024), (32, 4096, 1024),
-    # four row tiles at 49 ... 64 tokens for layers up to 12288 wide with K <= 4096
+    # 49 ... 64 tokens: 32 x 32, 32 x 64 and 64 x 64 tiles in k groups
     (64, 12288, 4096), (57, 4608, 3584), (64, 4096, 4096), (50, 3584, 3584), (61, 12288, 2048), (64, 1032, 576),
-    # tiled plans: 64 x 64 with K splits, 64 x 128, 128 x 128, 256 x 128, 128 x 256
-    (49, 4104, 4160), (64, 24576, 4096), (300, 1032, 576), (1024, 4096, 4096), (2100, 4104, 3584),
+    # tiled plans: k groups, 64 x 64, 64 x 128, 128 x 128, 256 x 128; 64 x 64 with K splits
+    (50, 1032, 16320), (57, 520, 16320), (200, 136, 20480), (49, 4104, 4160), (64, 24576, 4096), (300, 1032, 576), (1024, 4096, 4096), (2100, 4104, 3584),
     (4096, 8200, 4160), (513, 4104, 12288), (4096, 4096, 192), (4000, 4000, 4160), (3000, 12296, 3584),
     # 128 x 128 in two k groups: ragged M and N, an odd number of k steps with half a last step
     (1000, 3584, 19008), (1024, 3584, 18944), (1024, 4096, 12288),
@@ -154,8 +155,8 @@ W8_SHAPES = [
     # short M (<= 48 tokens): wide, mid-width and narrow layers; LDS or L2 activations
     (1, 24576, 4096), (16, 12288, 4096), (33, 4096, 4096), (48, 4096, 12288), (5, 4104, 4160),
     (17, 16392, 8192), (1, 8, 64), (3, 24, 192), (40, 8200, 12288),
-    # tiled plans: 64 x 64 with K splits, 64 x 128, 128 x 128, 256 x 128
-    (49, 4104, 4160), (64, 12288, 4096), (300, 1032, 576), (1024, 4096, 4096), (1024, 4096, 12288),
+    # tiled plans: k groups, 64 x 64 with K splits, 128 x 256
+    (50, 1032, 8192), (64, 4096, 10304), (49, 4104, 4160), (64, 12288, 4096), (300, 1032, 576), (1024, 4096, 4096), (1024, 4096, 12288),
     (2100, 4104, 3584), (4096, 12288, 4096), (4000, 4000, 4160),
     # 128 x 256 at 192 ... 511 of its tiles; 128 x 128 in two waves from 640 of its tiles (ragged M, N)
     (500, 12296, 4160), (1000, 12296, 4160), (520, 24576, 4096),

@@ -11,12 +11,14 @@ from oracle import oracle as O
 pytestmark = pytest.mark.gpu
 
 
-# 4-bit tiles: 32 x 32 (one k step for twelve groups; 31 steps), 32 x 64, 64 x 64
-# (a half-filled last k step), 64 x 128 in two and in three k groups, 128 x 128 in two;
-# then few rows: one or two row tiles, mostly padding, and a wide layer without k groups
+# 4-bit tiles: 32 x 32 (one k step for twelve groups, fragments only; 31 steps), 32 x 64,
+# 64 x 64 without k groups (K too shallow for them), 64 x 128 in three k groups; then few
+# rows: streamed but for 64 x 64 tiles at (33, 8200, 1088) and, row-major, 32 x 64 at
+# (20, 8200, 4160); 64 x 64 at 50 rows and a split across workgroups
 @pytest.mark.parametrize("M,N,K", [(49, 8, 64), (50, 136, 3968), (130, 2056, 4160), (77, 4104, 192), (250, 4104, 1088),
                                    (190, 8192, 1024), (400, 3592, 8256), (1000, 2048, 16448),
-                                   (9, 4616, 1088), (17, 4104, 192), (24, 136, 3968), (33, 8200, 1088), (41, 16392, 192)])
+                                   (9, 4616, 1088), (17, 4104, 192), (24, 136, 3968), (33, 8200, 1088), (41, 16392, 192),
+                                   (20, 8200, 4160), (50, 8200, 4160), (50, 1032, 16320)])
 def test_w4a4_k_groups(M, N, K):
     say(f"gemm k groups M={M} N={N} K={K}")
     rng = np.random.default_rng(M + N + K)
@@ -25,8 +27,9 @@ def test_w4a4_k_groups(M, N, K):
     check(Aq, Wq, K, O.gemm, 4)
 
 
-# 8-bit: the same tiles (128 x 128 in two k groups from 48 k steps), and (64, 4096,
-# 10304): 256 tiles of 32 x 32 and 161 k steps, split across workgroups
+# 8-bit: the same tiles, 128 x 128 in two k groups (49 steps), and (64, 4096, 10304):
+# 256 tiles of 32 x 32 and 161 k steps, split across workgroups; few rows, streamed but
+# for 64 x 64 and 64 x 128 tiles of row-major weights
 @pytest.mark.parametrize("M,N,K", [(49, 8, 64), (50, 136, 1984), (130, 2056, 2112), (250, 4104, 576), (190, 8192, 576),
                                    (400, 3592, 4160), (600, 4104, 3136), (64, 4096, 10304), (3, 4616, 576),
                                    (17, 136, 1984), (48, 8200, 576), (33, 16392, 2112)])

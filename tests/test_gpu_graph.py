@@ -47,9 +47,8 @@ def check_replays(g, outs, want, scramble):
 
 @pytest.mark.parametrize("M,K,N", [(64, 1024, 2048), (300, 4096, 1032), (1024, 3584, 18944)])
 def test_folded_step_graph(M, K, N):
-    """TAC-fused quantiser + fragment-order GEMM: the short-M four-tile plan at
-    64 tokens, the K-split plan and its reduction pass at 300 tokens
-    (300 x 1032 x 4096: four splits), the tiled plan at 1024 tokens."""
+    """TAC-fused quantiser + fragment-order GEMM: 32 x 32 tiles in k groups at 64
+    tokens, 32 x 64 ones at 300, larger tiles at 1024."""
     c = synth.small_case(40 + M, M, K, N, g=16)
     dm, du = synth.default_band(K)
     X, st = dev(c["X"]), dev(c["state"])
@@ -79,9 +78,10 @@ def test_folded_step_graph(M, K, N):
 
 
 @pytest.mark.parametrize("bits", [4, 8])
-def test_deep_k_gemm_graph(bits):
-    """The k-group plan (1024 x 3584 x 18944: 224 tiles of 128 x 128)."""
-    M, N, K = 1024, 3584, 18944
+@pytest.mark.parametrize("M,N,K", [(1024, 3584, 18944), (57, 520, 16320)])
+def test_deep_k_gemm_graph(bits, M, N, K):
+    """The k-group plan (1024 x 3584 x 18944: 224 tiles of 128 x 128), and the K split
+    across workgroups with its reduction pass (57 x 520 x 16320)."""
     rng = np.random.default_rng(bits)
     if bits == 4:
         Aq = dev(rng.integers(0, 256, (M, K // 2), dtype=np.uint8))
@@ -95,7 +95,7 @@ def test_deep_k_gemm_graph(bits):
     Y = torch.empty((M, N), dtype=torch.float16, device="cuda")
     acc = torch.empty((M, N), dtype=torch.int32, device="cuda")
     gws = torch.empty(max(sq.gemm_workspace_bytes(M, N, K, bits), 1), dtype=torch.uint8, device="cuda")
-    say(f"graph deep-K gemm bits={bits}")
+    say(f"graph deep-K gemm bits={bits} M={M} N={N} K={K}")
 
     def step():
         sq.w4a4_gemm_frag(Aq, s_a, Wf, s_w, Y=Y, acc=acc, want_acc=True, ws=gws, bits=bits)

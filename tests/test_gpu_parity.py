@@ -123,12 +123,16 @@ def test_transform_bit_exact(M, K):
 
 
 @pytest.mark.parametrize("M,K,dm,du", [(300, 1024, 256, 384), (1000, 4096, 128, 128), (70, 4096, 128, 128),
-                                        (513, 1024, 0, 384), (260, 1024, 256, 0), (2100, 4096, 128, 128)])
+                                        (513, 1024, 0, 384), (260, 1024, 256, 0), (2100, 4096, 128, 128),
+                                        # tiles of 64 rows, then of 128; half a last column tile at 1344 and 1088
+                                        (3400, 1024, 256, 384), (2800, 1344, 0, 384), (2800, 1344, 256, 0),
+                                        (8400, 1024, 256, 384), (9000, 1088, 0, 384), (9000, 1088, 256, 0)])
 @pytest.mark.parametrize("layout", ["random", "all_masked", "none_masked", "alternating", "blocks"])
 def test_transform_rows_grouped_by_state(M, K, dm, du, layout):
-    """Bands that hold whole 128-column tiles: rows are taken grouped by state and
-    row tiles of one state skip the tiles of the band they drop; the result is
-    the oracle's bit for bit, the dropped columns +0."""
+    """Bands that hold whole 128-column tiles: the tiled kernel takes rows grouped by
+    state, and row tiles of one state skip the tiles of the band they drop; the result
+    is the oracle's bit for bit, the dropped columns +0 (the split kernel's too: 300 x
+    1024, 70 x 4096, 513 x 1024 and 260 x 1024)."""
     rng = np.random.default_rng(M + K + dm)
     st = {"random": (rng.random(M) < 0.4), "all_masked": np.ones(M, bool), "none_masked": np.zeros(M, bool),
           "alternating": np.arange(M) % 2 == 1, "blocks": (np.arange(M) // 37) % 3 == 0}[layout].astype(np.uint8)
@@ -148,7 +152,7 @@ def test_transform_subnormal_products_and_signed_zeros():
     """A basis of subnormal and zero entries: products, chunk sums and totals are
     fp32 subnormals or signed zeros, kept (not flushed) and summed exactly as the
     oracle's IEEE chain does; zero columns give +0 for every row."""
-    M, K = 200, 512
+    M, K = 16500, 512
     X, st = _x(M, K, 12)
     P = synth.orthogonal(K, synth.rng_for(606, K)) * np.float32(2.0 ** -136)   # entries around 2^-140
     P[:, 5::7] = 0.0
@@ -156,7 +160,7 @@ def test_transform_subnormal_products_and_signed_zeros():
     P = P.astype(np.float32)
     assert (np.abs(P[P != 0]) < np.float32(2.0 ** -126)).all()
     say(f"transform subnormal basis M={M} K={K}")
-    for M_ in (M, 20):   # the pipelined kernel and the one for up to 32 rows
+    for M_ in (M, 9000, 200, 20):   # tiles of 128 and of 64 rows, and the split kernel
         xp = host(sq.sgat_transform(dev(X[:M_]), None, dev(P)))
         ref = O.transform(X[:M_], None, P, 0, 0, threads=THREADS)
         assert (ref != 0).any() and (np.abs(ref[ref != 0]) < np.float32(2.0 ** -126)).any()
@@ -208,14 +212,15 @@ def _codes(M, K, seed, lo=-7, hi=7):
 # every launch plan: short M, 1 to 3 row tiles of 16 (activations shared in LDS for
 # wide 4-bit layers, expanded once for one row tile, per wave for more; a half
 # last k step and a partial last workgroup; K split inside the workgroup 1, 2, 4
-# or 8 ways), the tiled shapes with ragged last tiles and the split-K path
+# or 8 ways), the tiled shapes with ragged last tiles, k groups within a workgroup, and
+# K split across workgroups (64 x 512 x 18944 and 50 x 1032 x 16320)
 GEMM_SHAPES = [(1, 8, 64), (16, 4096, 4096), (5, 4104, 4096), (9, 136, 192), (16, 24, 18944),
                (16, 12288, 4096), (16, 4096, 12288), (9, 16392, 192), (16, 32768, 256), (33, 520, 1024),
                (16, 24576, 4096), (7, 37888, 3584), (3, 12304, 4032), (1, 12288, 64), (16, 16392, 8192),
                (11, 2056, 4160), (4096, 8200, 192), (4096, 8200, 4160),
                (64, 24576, 4096), (48, 12304, 4032), (20, 16384, 8192), (64, 16392, 8192), (40, 4104, 12288),
                (77, 200, 192), (128, 256, 512), (300, 136, 4096), (300, 16384, 64), (1024, 1024, 1024),
-               (1000, 8200, 64), (2100, 12296, 64), (513, 4104, 3584), (64, 512, 18944),
+               (1000, 8200, 64), (2100, 12296, 64), (513, 4104, 3584), (64, 512, 18944), (50, 1032, 16320),
                (4096, 4096, 192), (4000, 4000, 4160), (1000, 12296, 4160),
                # two k groups per tile: ragged M and N, an odd number of k steps (half a last step at 4 bits)
                (1000, 4000, 12352), (1024, 3584, 18944), (1000, 3584, 19008)]
@@ -287,17 +292,18 @@ def test_w8a8_gemm_at_the_largest_K():
     assert_bits(host(acc), ref.astype(np.int32), "acc")
 
 
-def test_gemm_split_and_unsplit_agree():
-    """Rows computed through the split-K path (few tiles) and through the short-M
-    kernels equal the same rows inside a tall M that takes the single-pass path."""
-    K, N = 12288, 4096
+@pytest.mark.parametrize("K,N,few", [(12288, 4096, (96, 48, 16)), (20480, 4096, (64, 50)), (16320, 1032, (50,))])
+def test_gemm_split_and_unsplit_agree(K, N, few):
+    """Rows of small grids, which share a tile's K among k groups (12288) or split it
+    across workgroups (16320, 20480), and of the short-M kernels (16 rows), equal the
+    same rows inside a tall M of larger tiles."""
     Aq = _codes(2048, K, 7)
     Wq = _codes(N, K, 8)
     s_a = np.random.default_rng(9).uniform(0.1, 2, 2048).astype(np.float32)
     s_w = np.random.default_rng(10).uniform(1e-3, 2e-3, N).astype(np.float32)
-    assert sq.gemm_workspace_bytes(96, N, K) > 0 and sq.gemm_workspace_bytes(2048, N, K) == 0
+    assert sq.gemm_workspace_bytes(few[0], N, K) > 0
     big = host(sq.w4a4_gemm(dev(Aq), dev(s_a), dev(Wq), dev(s_w)))
-    for m in (96, 48, 16):
+    for m in few:
         small = host(sq.w4a4_gemm(dev(Aq[:m]), dev(s_a[:m]), dev(Wq), dev(s_w)))
         assert_bits(small, big[:m], f"{m} rows vs the single-pass rows")
 

@@ -13,10 +13,13 @@ pytestmark = pytest.mark.gpu
 
 # (M, K, blocks of 16 x 16 per tile as rows x columns): one wave (K = 64) up to 16
 # chunks on 16 waves (4096), 17 on 16 (4160: a second round of one partial chunk)
-# and 9 or 16 on 8
-@pytest.mark.parametrize("M,K,tile", [(1, 64, "1x1"), (17, 64, "1x1"), (33, 320, "1x1"), (31, 2240, "1x2"),
-                                      (16, 4160, "1x1"), (64, 2112, "1x4"), (50, 4160, "2x4"), (128, 4096, "2x4"),
-                                      (250, 4096, "4x4"), (1000, 512, "1x4"), (2000, 896, "4x4")])
+# and 5, 9 or 16 on 8
+SHAPES = [(1, 64, "1x1"), (17, 64, "1x1"), (33, 320, "1x1"), (31, 2240, "1x2"),
+          (16, 4160, "1x1"), (64, 2112, "1x4"), (50, 4160, "2x4"), (128, 4096, "2x4"),
+          (250, 4096, "4x4"), (1000, 512, "1x4"), (2000, 896, "2x4"), (866, 1152, "4x4")]
+
+
+@pytest.mark.parametrize("M,K,tile", SHAPES)
 def test_transform_split_bit_exact(M, K, tile):
     say(f"transform split M={M} K={K} tile {tile}")
     rng = np.random.default_rng(M * K)

@@ -7,7 +7,8 @@ import subprocess
 
 import pytest
 
-from gemm_kernels import KERNELS, kernel_of
+from gemm_kernels import KERNELS, SPLIT_K, kernel_of
+from test_gpu_transform_split import SHAPES as SPLIT_TRANSFORM
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2606_04945_amd", "csrc")
@@ -69,6 +70,17 @@ def test_every_gemm_kernel_is_reached(plans):
     for name, (M, N, K) in KERNELS.items():
         bits, frag = int(name[0]), "fragments" in name
         assert kernel_of(gemm(plans, M, N, K, bits, frag), M, bits, frag) == name
+
+
+def test_split_shapes_split(plans):
+    """What the scratch tests call does use the scratch, the first call the most of it."""
+    scratch = []
+    for M, N, K in SPLIT_K:
+        for frag in (False, True):
+            p = gemm(plans, M, N, K, 4, frag)
+            assert p["splits"] > 1
+            scratch.append(p["splits"] * M * N * 4)
+    assert scratch == sorted(scratch, reverse=True) and scratch[0] > scratch[-1] and scratch[0] <= 16 << 20
 
 
 def test_no_plan_asks_for_another_gemm_kernel(plans):
@@ -144,6 +156,13 @@ def test_fixed_order_transform_takes_the_faster_kernel(plans, M, K, tiled, split
     o = (ctypes.c_int * 3)()
     us = split[SPLIT_BLOCKS.index((o[0], o[1]))] if plans.split(M, K, 0, 0, 0, o) else tiled
     assert us <= 1.05 * min(tiled, *split)
+
+
+def test_split_transform_shapes_take_their_blocks(plans):
+    o = (ctypes.c_int * 3)()
+    for M, K, tile in SPLIT_TRANSFORM:
+        for dm, du, gated in [(0, 0, 0), (K // 32, K // 32, 1), (0, 13, 1), (K // 2, 17, 1)]:
+            assert plans.split(M, K, dm, du, gated, o) and f"{o[0]}x{o[1]}" == tile
 
 
 def test_fixed_order_transform_blocks_fit(plans):

@@ -10,6 +10,7 @@ import torch
 
 import paper_2606_04945_amd as sq
 from paper_2606_04945_amd import _lib as L
+from gemm_kernels import SPLIT_K
 from oracle import oracle as O
 from gpu_util import assert_bits, assert_y, dev, host, say
 
@@ -36,9 +37,9 @@ def _noalloc(Aq, s_a, Wf, s_w, M, N, K, stream=None):
 
 
 # (M, N, K): the first two split K across workgroups (the scratch holds the
-# partial sums), the second smaller than the first; then a short-M and a tiled
-# shape that need no scratch
-SHAPES = [(100, 520, 4096), (70, 264, 2048), (16, 4096, 4096), (300, 1024, 512)]
+# partial sums), the second smaller than the first; then two shapes in k groups,
+# a short-M one and a tiled one that need no scratch
+SHAPES = [*SPLIT_K, (100, 520, 4096), (70, 264, 2048), (16, 4096, 4096), (300, 1024, 512)]
 
 
 def test_noalloc_matches_workspace_entry_point():
