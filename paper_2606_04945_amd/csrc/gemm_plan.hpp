@@ -153,8 +153,9 @@ Plan choose_frag_short(int M, int N, int K, int bits) {
     return p;
 }
 
-// Up to 48 rows: the kernels that stream the weights into registers, or the tiles in
-// k groups, whose workgroup reads a weight once for all its rows.  The streaming
+// Up to 48 rows: the kernels that stream the weights into registers, or tiles, whose
+// workgroup reads a weight once for all its rows (in k groups, but for layers too wide
+// for them).  The streaming
 // kernels' time grows with the row tiles (each expands and multiplies on its own
 // wave) and most where the activations no longer fit in LDS; the tiles keep fewer
 // weights in flight per wave, so they gain least on weights that come from HBM.
