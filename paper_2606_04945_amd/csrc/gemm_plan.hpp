@@ -210,8 +210,8 @@ bool stream_weights(int M, int N, int K, int bits, bool frag) {
 // and the split's second launch costs about 4 us; 8000 shapes of 49 ... 2000 rows,
 // graph-replayed over 340 MB of weights in turn, other plan -> k groups:
 //  - a shallow K leaves most groups idle: 128 x 128 x 64 3.0 -> 3.8 us, 200 x 8192 x
-//    512 5.1 -> 6.1 (up to 64 rows of fragment-ordered 4-bit weights up to 12288 wide
-//    k groups are the faster ones there too);
+//    512 5.1 -> 6.1, 8-bit 160 x 1872 x 576 4.6 -> 5.1 (up to 64 rows of fragment-ordered
+//    4-bit weights up to 12288 wide k groups are the faster ones there too);
 //  - a deep K on few tiles: the split has more workgroups than CUs to share it, 64 x
 //    64 x 65536 17 -> 29 us, 8-bit 250 x 64 x 65536 19 -> 61.  32 x 32 tiles hold up
 //    to 8 steps a group, to 13 where the split is not two steps shorter or the
@@ -229,10 +229,10 @@ bool k_groups_faster(const Plan& p, const Plan& other, int M, int N, int nk, int
             if (shallow && nk <= (bits == 8 ? 6 : 3)) return false;
             return w10 <= 8 || (w10 <= 13 && (M > 64 || other.per >= w10 - 1)) || (w10 <= 16 && other.per >= w10 - 2);
         case 11:
-            if (shallow && nk <= 6) return false;
+            if (shallow && nk <= (bits == 4 ? 6 : frag ? 9 : 7)) return false;
             return w11 <= (other.splits <= 4 ? 48 : other.splits <= 6 ? 24 : 16);
         case 12:
-            if (shallow && nk <= 7) return false;
+            if (shallow && nk <= (bits == 4 ? 7 : 9)) return false;
             return w12 <= (bits == 8 ? 64 : 40) || other.splits < 4;
         case 13: return other.cfg != 2 || nk >= (bits == 8 ? 20 : 32);
         default: return true;

@@ -123,6 +123,7 @@ def test_few_rows_take_the_faster_kernel(plans, M, N, K, bits, frag, streamed, t
     (57, 14336, 256, 4, True, 4.0, 4.8), (600, 3072, 2048, 4, True, 9.3, 9.8), (64, 2048, 9216, 8, False, 13.1, 16.6),
     (64, 64, 65536, 4, True, 17.4, 28.7), (64, 8, 65536, 8, True, 16.7, 44.1), (250, 64, 65536, 8, False, 19.3, 60.6),
     (128, 4096, 4096, 4, True, 12.5, 7.1), (50, 3584, 18944, 4, True, 17.7, 15.2), (100, 1024, 9216, 8, True, 15.2, 11.0),
+    (160, 1872, 576, 8, True, 4.61, 5.12), (354, 2048, 512, 8, False, 4.56, 4.85),
     (128, 512, 512, 4, True, 3.86, 3.85), (512, 3584, 18944, 8, True, 96.4, 71.1), (300, 10240, 3072, 8, True, 23.8, 20.1)])
 def test_small_grids_take_the_faster_tiles(plans, M, N, K, bits, frag, without, groups):
     assert (gemm(plans, M, N, K, bits, frag)["cfg"] in K_GROUPS) == (groups < without)
