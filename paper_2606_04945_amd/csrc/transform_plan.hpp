@@ -71,9 +71,10 @@ constexpr int split_waves(int blocks) { return blocks <= 4 ? 16 : 8; }
 // Time of a tile shape, in 16 x 16 x 256 block chunks of the fp32 matrix cores
 // per SIMD (64 MFMAs, 0.85 us at 2.4 GHz; measured 0.8-1.2 us each), the largest of
 //  - the matrix cores: the busiest CU's workgroups, as many side by side as their
-//    waves fit, times their rounds of chunks; twice that for 4 x 4 blocks with up to
-//    four waves, whose registers leave a SIMD one or two (3612 x 512: 39.6 us, the
-//    smaller shapes 22.7 - 30.3);
+//    waves fit, times their rounds of chunks; twice that for 4 x 4 and 2 x 4 blocks with
+//    up to four waves, whose registers leave a SIMD one or two (3612 x 512: 39.6 us on
+//    4 x 4, the smaller shapes 22.7 - 30.3; 6877 x 256 with the quantiser behind it, so
+//    that x comes from memory again: 31.2 on 2 x 4, 23.6 on 1 x 4, 26.3 tiled);
 //  - P's bytes at 4.9 TB/s, more where fewer than 192 workgroups read them (16 x
 //    8192: 57 us on 256 workgroups, 66 on 128; 16 x 12288: 127 us on 192);
 //  - P read again by every row tile: 64-, 128- and 256-byte runs (CB = 1, 2, 4) came
@@ -86,7 +87,7 @@ inline SplitShape split_cost(int rb, int cb, int M, int K) {
     const long n = (wgs + kCus - 1) / kCus, side = cap / W;
     const long passes = (n + side - 1) / side, at_once = n < side ? n : side;
     long cost = passes * ((at_once * W + 3) / 4) * ((nch + W - 1) / W) * rb * cb;
-    if (rb * cb == 16 && W <= 4) cost *= 2;
+    if (rb * cb >= 8 && W <= 4) cost *= 2;
     const long p_read = (long)K * K;                 // x 1400000; divided last, small K count too
     const long mem = p_read * 192 / (1400000 * (wgs < 192 ? wgs : 192));
     const long again = p_read * rows * (cb == 1 ? 16 : cb == 2 ? 10 : 7) / (16 * 1400000);

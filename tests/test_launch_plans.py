@@ -150,9 +150,12 @@ SPLIT_BLOCKS = ((4, 4), (2, 4), (1, 4), (1, 2), (1, 1))
 @pytest.mark.parametrize("M,K,tiled,split", [
     (2705, 1344, 95.3, (146.0, 133.6, 113.2, 120.5, 153.9)), (4029, 1280, 139.5, (183.6, 188.2, 154.4, 158.3, 223.4)),
     (2655, 2624, 358.1, (391.2, 403.9, 400.6, 436.0, 598.8)), (3612, 512, 27.7, (39.7, 23.2, 22.7, 28.0, 30.3)),
-    (3848, 512, 28.3, (40.6, 24.1, 23.6, 30.6, 33.9)), (191, 4096, 165.5, (73.7, 74.9, 62.2, 83.7, 102.9)),
+    (191, 4096, 165.5, (73.7, 74.9, 62.2, 83.7, 102.9)),
     (95, 4096, 165.9, (72.8, 40.6, 42.6, 45.2, 55.5)), (41, 4096, 165.4, (72.0, 39.2, 24.0, 30.3, 30.1)),
-    (641, 4096, 268.4, (217.2, 221.0, 216.1, 284.4, 376.5)), (94, 11648, 461.1, (424.7, 328.9, 315.8, 398.7, 572.6))])
+    (641, 4096, 268.4, (217.2, 221.0, 216.1, 284.4, 376.5)),
+    # with the quantiser behind it
+    (6877, 256, 26.3, (34.2, 31.2, 23.6, 24.0, 25.1)), (4946, 320, 28.0, (36.1, 31.4, 24.1, 25.8, 27.4)),
+    (94, 11648, 461.1, (424.7, 328.9, 315.8, 398.7, 572.6))])
 def test_fixed_order_transform_takes_the_faster_kernel(plans, M, K, tiled, split):
     o = (ctypes.c_int * 3)()
     us = split[SPLIT_BLOCKS.index((o[0], o[1]))] if plans.split(M, K, 0, 0, 0, o) else tiled
