@@ -297,7 +297,8 @@ Plan choose_plan(int M, int N, int K, int bits, bool k_groups, bool frag = false
             p.cfg = 3;
             p.waves = kw;
         }
-    } else if (tiles(128, 128) > 128 && tiles(128, 128) <= 256 && nk >= (bits == 8 ? (!k_groups ? 64 : tiles(128, 128) > 160 ? 48 : 49) : 128)) {
+    } else if (tiles(128, 128) > 128 && tiles(128, 128) <= 256 &&
+               nk >= (bits == 4 ? 128 : !k_groups ? 64 : tiles(128, 128) > 160 ? 48 : 49)) {
         // at most one 128 x 128 tile per CU and a deep K: two k groups of four
         // waves per tile (interleaved timings with rotating weights against the
         // plans below: 8-bit 1024 x 4096 x 4096 13 % faster, 1024 x 4096 x 12288

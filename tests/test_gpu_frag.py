@@ -62,7 +62,8 @@ SHAPES = [
     # 49 ... 64 tokens: 32 x 32, 32 x 64 and 64 x 64 tiles in k groups
     (64, 12288, 4096), (57, 4608, 3584), (64, 4096, 4096), (50, 3584, 3584), (61, 12288, 2048), (64, 1032, 576),
     # tiled plans: k groups, 64 x 64, 64 x 128, 128 x 128, 256 x 128; 64 x 64 with K splits
-    (50, 1032, 16320), (57, 520, 16320), (200, 136, 20480), (49, 4104, 4160), (64, 24576, 4096), (300, 1032, 576), (1024, 4096, 4096), (2100, 4104, 3584),
+    (50, 1032, 16320), (57, 520, 16320), (200, 136, 20480), (49, 4104, 4160), (64, 24576, 4096),
+    (300, 1032, 576), (1024, 4096, 4096), (2100, 4104, 3584),
     (4096, 8200, 4160), (513, 4104, 12288), (4096, 4096, 192), (4000, 4000, 4160), (3000, 12296, 3584),
     # 128 x 128 in two k groups: ragged M and N, an odd number of k steps with half a last step
     (1000, 3584, 19008), (1024, 3584, 18944), (1024, 4096, 12288),
@@ -156,7 +157,8 @@ W8_SHAPES = [
     (1, 24576, 4096), (16, 12288, 4096), (33, 4096, 4096), (48, 4096, 12288), (5, 4104, 4160),
     (17, 16392, 8192), (1, 8, 64), (3, 24, 192), (40, 8200, 12288),
     # tiled plans: k groups, 64 x 64 with K splits, 128 x 256
-    (50, 1032, 8192), (64, 4096, 10304), (49, 4104, 4160), (64, 12288, 4096), (300, 1032, 576), (1024, 4096, 4096), (1024, 4096, 12288),
+    (50, 1032, 8192), (64, 4096, 10304), (49, 4104, 4160), (64, 12288, 4096), (300, 1032, 576),
+    (1024, 4096, 4096), (1024, 4096, 12288),
     (2100, 4104, 3584), (4096, 12288, 4096), (4000, 4000, 4160),
     # 128 x 256 at 192 ... 511 of its tiles; 128 x 128 in two waves from 640 of its tiles (ragged M, N)
     (500, 12296, 4160), (1000, 12296, 4160), (520, 24576, 4096),
